@@ -2149,6 +2149,102 @@ __global__ __launch_bounds__(256) void k_probe_philox(uint32_t* out, uint32_t ca
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+template <int LAYOUT, int L>
+void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t model,
+                    hipStream_t stream) {
+  // after the tile image and the reduction area: the Gaussian threshold table,
+  // or the +-J plane areas (one per wave)
+  // after the tile image: the reduction area and the Gaussian threshold table,
+  // or the +-J plane areas (one per wave; the reduction area lies over them)
+  const size_t after = model == kModelGauss16
+                           ? (size_t)kPlaneAreaBytes * split + (size_t)(kGaussDEMax + 1) * 8
+                           : (size_t)kPlaneAreaBytes * split;
+  static_assert(kPlaneAreaBytes >= 8 * 64, "the reduction area lies over the plane areas");
+  const size_t lds = (size_t)L * L * L * 8 + after;
+  if (model == kModelReal) {
+    if (split == 8)
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelReal>), dim3(g.blocks), dim3(64 * 8), lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelReal>), dim3(g.blocks), dim3(64 * 4), lds,
+                         stream, B, g);
+  } else if (model == kModelGauss16) {
+    if (split == 8)
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelGauss16>), dim3(g.blocks), dim3(64 * 8), lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelGauss16>), dim3(g.blocks), dim3(64 * 4), lds,
+                         stream, B, g);
+  } else {
+    if (split == 8)
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelPm>), dim3(g.blocks), dim3(64 * 8), lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelPm>), dim3(g.blocks), dim3(64 * 4), lds,
+                         stream, B, g);
+  }
+}
+
+template <int LAYOUT, int L>
+void launch_energy_l(const BatchDev& B, const Group& g, uint32_t model, bool check,
+                     hipStream_t stream) {
+  const size_t lds = (size_t)L * L * L * 8;
+  if (model == kModelReal) {
+    if (check)
+      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelReal, true>), dim3(g.blocks), dim3(64), lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelReal, false>), dim3(g.blocks), dim3(64), lds,
+                         stream, B, g);
+  } else if (model == kModelGauss16) {
+    if (check)
+      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelGauss16, true>), dim3(g.blocks), dim3(64), lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelGauss16, false>), dim3(g.blocks), dim3(64),
+                         lds, stream, B, g);
+  } else {
+    if (check)
+      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelPm, true>), dim3(g.blocks), dim3(64), lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelPm, false>), dim3(g.blocks), dim3(64), lds,
+                         stream, B, g);
+  }
+}
+
+template <int LAYOUT, int L>
+void launch_link_overlap_l(const DevPop& a, const DevPop& b, uint32_t cur_a, uint32_t cur_b,
+                           uint32_t* part, uint32_t tiles, hipStream_t stream) {
+  hipLaunchKernelGGL((k_link_overlap<LAYOUT, L>), dim3(tiles), dim3(64), 0, stream, a, b, cur_a,
+                     cur_b, part);
+}
+
+// This file is compiled once per lattice size with PA_KERNEL_L = L, for the
+// kernels that are instantiated per L (one object each, built in parallel),
+// and once without it for everything else.
+#define PA_INSTANTIATE(EXTERN, LAYOUT, LL)                                                      \
+  EXTERN template void launch_sweep_l<LAYOUT, LL>(const BatchDev&, const Group&, uint32_t,      \
+                                                  uint32_t, hipStream_t);                       \
+  EXTERN template void launch_energy_l<LAYOUT, LL>(const BatchDev&, const Group&, uint32_t,     \
+                                                   bool, hipStream_t);                          \
+  EXTERN template void launch_link_overlap_l<LAYOUT, LL>(const DevPop&, const DevPop&, uint32_t, \
+                                                         uint32_t, uint32_t*, uint32_t,         \
+                                                         hipStream_t);
+#ifdef PA_KERNEL_L
+PA_INSTANTIATE(, 1, PA_KERNEL_L)
+PA_INSTANTIATE(, 2, PA_KERNEL_L)
+#else
+#define PA_EXTERN_L(LL) PA_INSTANTIATE(extern, 1, LL) PA_INSTANTIATE(extern, 2, LL)
+PA_EXTERN_L(4)
+PA_EXTERN_L(6)
+PA_EXTERN_L(8)
+PA_EXTERN_L(10)
+PA_EXTERN_L(12)
+PA_EXTERN_L(14)
+PA_EXTERN_L(16)
+#undef PA_EXTERN_L
+
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t stream) {
   if (n == 0) return hipSuccess;
   const uint32_t grid = (uint32_t)std::min<size_t>((n + 255) / 256, 1024);
@@ -2233,70 +2329,6 @@ hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream)
   return hipGetLastError();
 }
 
-template <int LAYOUT, int L>
-void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t model,
-                    hipStream_t stream) {
-  // after the tile image and the reduction area: the Gaussian threshold table,
-  // or the +-J plane areas (one per wave)
-  // after the tile image: the reduction area and the Gaussian threshold table,
-  // or the +-J plane areas (one per wave; the reduction area lies over them)
-  const size_t after = model == kModelGauss16
-                           ? (size_t)kPlaneAreaBytes * split + (size_t)(kGaussDEMax + 1) * 8
-                           : (size_t)kPlaneAreaBytes * split;
-  static_assert(kPlaneAreaBytes >= 8 * 64, "the reduction area lies over the plane areas");
-  const size_t lds = (size_t)L * L * L * 8 + after;
-  if (model == kModelReal) {
-    if (split == 8)
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelReal>), dim3(g.blocks), dim3(64 * 8), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelReal>), dim3(g.blocks), dim3(64 * 4), lds,
-                         stream, B, g);
-  } else if (model == kModelGauss16) {
-    if (split == 8)
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelGauss16>), dim3(g.blocks), dim3(64 * 8), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelGauss16>), dim3(g.blocks), dim3(64 * 4), lds,
-                         stream, B, g);
-  } else {
-    if (split == 8)
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelPm>), dim3(g.blocks), dim3(64 * 8), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelPm>), dim3(g.blocks), dim3(64 * 4), lds,
-                         stream, B, g);
-  }
-}
-
-template <int LAYOUT, int L>
-void launch_energy_l(const BatchDev& B, const Group& g, uint32_t model, bool check,
-                     hipStream_t stream) {
-  const size_t lds = (size_t)L * L * L * 8;
-  if (model == kModelReal) {
-    if (check)
-      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelReal, true>), dim3(g.blocks), dim3(64), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelReal, false>), dim3(g.blocks), dim3(64), lds,
-                         stream, B, g);
-  } else if (model == kModelGauss16) {
-    if (check)
-      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelGauss16, true>), dim3(g.blocks), dim3(64), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelGauss16, false>), dim3(g.blocks), dim3(64),
-                         lds, stream, B, g);
-  } else {
-    if (check)
-      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelPm, true>), dim3(g.blocks), dim3(64), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_energy<LAYOUT, L, kModelPm, false>), dim3(g.blocks), dim3(64), lds,
-                         stream, B, g);
-  }
-}
-
 #define PA_L_SWITCH(FN, LAYOUT)      \
   switch (L) {                       \
     case 4: FN<LAYOUT, 4>(B, g, model, check, stream); break;   \
@@ -2371,34 +2403,27 @@ hipError_t launch_overlap(const BatchDev& B, const Group& g, const uint32_t* pai
   return hipGetLastError();
 }
 
-template <int LAYOUT>
-static hipError_t launch_link_overlap_l(const DevPop& a, const DevPop& b, uint32_t cur_a,
-                                        uint32_t cur_b, uint32_t* part, uint32_t tiles,
-                                        hipStream_t stream) {
-  switch (a.L) {
-#define PA_LINK_CASE(LL)                                                                       \
-  case LL:                                                                                     \
-    hipLaunchKernelGGL((k_link_overlap<LAYOUT, LL>), dim3(tiles), dim3(64), 0, stream, a, b,   \
-                       cur_a, cur_b, part);                                                    \
-    break;
-    PA_LINK_CASE(4) PA_LINK_CASE(6) PA_LINK_CASE(8) PA_LINK_CASE(10) PA_LINK_CASE(12)
-    PA_LINK_CASE(14) PA_LINK_CASE(16)
-#undef PA_LINK_CASE
-    default:
-      return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_link_overlap(const DevPop& a, const DevPop& b, uint32_t cur_a, uint32_t cur_b,
                                uint32_t* part, unsigned long long* hist, hipStream_t stream) {
   if (a.L != b.L || a.layout != b.layout) return hipErrorInvalidValue;
   const uint32_t tiles = min(a.capacity, b.capacity) / 64;
   const uint32_t nbins = 3 * a.N + 1;
-  hipError_t e = hipSuccess;
   if (tiles) {
-    e = a.layout == 2 ? launch_link_overlap_l<2>(a, b, cur_a, cur_b, part, tiles, stream)
-                      : launch_link_overlap_l<1>(a, b, cur_a, cur_b, part, tiles, stream);
+    switch (a.L) {
+#define PA_LINK_CASE(LL)                                                             \
+  case LL:                                                                           \
+    if (a.layout == 2)                                                               \
+      launch_link_overlap_l<2, LL>(a, b, cur_a, cur_b, part, tiles, stream);         \
+    else                                                                             \
+      launch_link_overlap_l<1, LL>(a, b, cur_a, cur_b, part, tiles, stream);         \
+    break;
+      PA_LINK_CASE(4) PA_LINK_CASE(6) PA_LINK_CASE(8) PA_LINK_CASE(10) PA_LINK_CASE(12)
+      PA_LINK_CASE(14) PA_LINK_CASE(16)
+#undef PA_LINK_CASE
+      default:
+        return hipErrorInvalidValue;
+    }
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_link_reduce, dim3((nbins + 255) / 256), dim3(256), 0, stream, part, nbins,
@@ -2459,5 +2484,6 @@ hipError_t launch_probe_philox(uint32_t* out, uint32_t calls, hipStream_t stream
   hipLaunchKernelGGL(k_probe_philox, dim3(kProbeThreads / 256), dim3(256), 0, stream, out, calls);
   return hipGetLastError();
 }
+#endif  // PA_KERNEL_L
 
 }  // namespace pa
