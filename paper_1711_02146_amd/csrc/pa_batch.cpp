@@ -130,7 +130,7 @@ int capture_step(pa_batch* b) {
        pa::launch_family(B, b->g_slots, true, s) == hipSuccess &&
        pa::launch_record(B, b->g_perpop, s) == hipSuccess;
   for (const auto& pg : b->g_pairs)
-    ok = ok && pa::launch_overlap(B, pg.g, b->d_pair_pops, pg.layout, true, 0, 0, s) == hipSuccess;
+    ok = ok && pa::launch_overlap(B, pg.g, b->d_pair_pops, pg.layout, s) == hipSuccess;
   ok = ok && pa::launch_advance(b->d_ctr, s) == hipSuccess;
   hipGraph_t g = nullptr;
   const hipError_t e = hipStreamEndCapture(s, &g);
@@ -274,8 +274,8 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
     for (uint32_t k = 0; k < n_pairs; ++k) {
       if (pops[pairs[2 * k]]->dev.layout != layout) continue;
       ids.push_back(k);
-      nb.push_back(std::min(pops[pairs[2 * k]]->dev.capacity,
-                            pops[pairs[2 * k + 1]]->dev.capacity) / 64);
+      nb.push_back(pa::blocks_overlap(std::min(pops[pairs[2 * k]]->dev.capacity,
+                                               pops[pairs[2 * k + 1]]->dev.capacity)));
     }
     if (!ids.empty()) b->g_pairs.push_back({layout, add_group(ids, nb)});
   }

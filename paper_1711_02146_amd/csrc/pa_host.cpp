@@ -125,7 +125,7 @@ bool make_layout(const pa_params* p, Layout* out) {
   l.off_ovl = take(65 * 8);
   l.off_lovl = take((size_t)(3 * l.N + 1) * 8);
   l.off_lpart = take((size_t)pa::kLinkCopies * (3 * l.N + 1) * 4);
-  l.off_pops = take(2 * sizeof(DevPop));
+  l.off_pops = take(sizeof(DevPop));
   l.off_meta = take(sizeof(MetaU32));
   // PA_MODEL_GAUSS: the he and threshold tables of every (site, pattern), and
   // one reduction partial per workgroup of the slot kernels
@@ -1247,14 +1247,12 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
   in->d_pops = reinterpret_cast<DevPop*>(w + l.off_pops);
   in->d_meta = reinterpret_cast<MetaU32*>(w + l.off_meta);
   MetaU32& mt = in->meta;
-  mt.pop0[0] = 0; mt.pop0[1] = 1;
+  mt.pop0[0] = 0; mt.pop0[1] = 0;
   mt.perpop[0] = 0; mt.perpop[1] = 1;
   mt.slots[0] = 0; mt.slots[1] = pa::blocks_slots(l.capacity);
   mt.hist[0] = 0; mt.hist[1] = pa::blocks_hist(l.capacity);
   mt.tiles[0] = 0; mt.tiles[1] = pa::blocks_sweep(l.capacity);
   mt.etiles[0] = 0; mt.etiles[1] = l.capacity / 64;
-  mt.pair_pops[0] = 0; mt.pair_pops[1] = 1;
-  mt.pairs[0] = 0; mt.pairs[1] = 0;
   mt.rsum[0] = 0; mt.rsum[1] = std::min(pa::blocks_slots(l.capacity), pa::kRealSumBlocks);
 
   auto fail = [&](int rc) {
@@ -1268,8 +1266,7 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
                     (size_t)l.n_levels * sizeof(pa::TableEntry)) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&in->h_ovl), 65 * 8) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&in->h_lovl), (size_t)(3 * l.N + 1) * 8) !=
-          hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&in->h_meta), sizeof(MetaU32)) != hipSuccess)
+          hipSuccess)
     return fail(PA_EDEVICE);
   in->h_sc = reinterpret_cast<DevScalars*>(reinterpret_cast<uint8_t*>(in->h_hist) + l.hist_bytes);
   in->h_rs = reinterpret_cast<pa::RealScalars*>(in->h_sc + 1);
@@ -1434,7 +1431,6 @@ int pa_free(pa_instance* in) {
   if (in->h_table) (void)hipHostFree(in->h_table);
   if (in->h_ovl) (void)hipHostFree(in->h_ovl);
   if (in->h_lovl) (void)hipHostFree(in->h_lovl);
-  if (in->h_meta) (void)hipHostFree(in->h_meta);
   if (in->h_gthr) (void)hipHostFree(in->h_gthr);
   if (in->gthr_copied) (void)hipEventDestroy(in->gthr_copied);
   for (hipEvent_t e : in->sweep_ev)
@@ -1576,23 +1572,8 @@ int pa_overlap_hist(pa_instance* a, pa_instance* b, uint32_t nbins, uint64_t* hi
   rc = materialize(b);
   if (rc) return rc;
   PA_HIP(b, hipStreamSynchronize(b->stream));
-  // a's set holds a in slot 0 and b in slot 1; one member pair, tiles of the smaller capacity
-  *a->h_meta = a->meta;
-  a->h_meta->pairs[1] = std::min(a->dev.capacity, b->dev.capacity) / 64;
-  PA_HIP(a, hipMemcpyAsync(a->d_pops + 1, &b->dev, sizeof(DevPop), hipMemcpyHostToDevice,
-                           a->stream));
-  PA_HIP(a, hipMemcpyAsync(a->d_meta, a->h_meta, sizeof(MetaU32), hipMemcpyHostToDevice,
-                           a->stream));
   PA_HIP(a, pa::launch_fill_u32(reinterpret_cast<uint32_t*>(a->dev.ovl_hist), 0u, 130, a->stream));
-  pa::BatchDev B = one_set(a, plain_step(a->cur));
-  B.n_pops = 2;
-  pa::Group g{};
-  g.pop = a->d_meta->pop0;
-  g.start = a->d_meta->pairs;
-  g.n = 1;
-  g.blocks = a->h_meta->pairs[1];
-  PA_HIP(a, pa::launch_overlap(B, g, a->d_meta->pair_pops, a->dev.layout, false, a->cur, b->cur,
-                               a->stream));
+  PA_HIP(a, pa::launch_overlap_pair(a->dev, b->dev, a->cur, b->cur, a->stream));
   PA_HIP(a, hipMemcpyAsync(a->h_ovl, a->dev.ovl_hist, 65 * 8, hipMemcpyDeviceToHost, a->stream));
   PA_HIP(a, hipStreamSynchronize(a->stream));
   for (int i = 0; i < 65; ++i) hist_out[i] = a->h_ovl[i];

@@ -19,14 +19,12 @@ using pa::SiteEntry;
 
 // Group tables of calls on one instance (two-entry start arrays {0, blocks}).
 struct MetaU32 {
-  uint32_t pop0[2];       // {0, 1}: member populations of a one-population set (+ partner)
+  uint32_t pop0[2];       // {0, 0}: the member population of a one-population set
   uint32_t perpop[2];     // one workgroup
   uint32_t slots[2];      // capacity / 256 workgroups
   uint32_t hist[2];       // histogram workgroups
   uint32_t tiles[2];      // sweep workgroups
   uint32_t etiles[2];     // one-wave tiles (energy recompute)
-  uint32_t pair_pops[2];  // {0, 1}: the instance and its overlap partner
-  uint32_t pairs[2];      // overlap workgroups, set per call
   uint32_t rsum[2];       // PA_MODEL_GAUSS weight reductions: min(capacity / 256, kRealSumBlocks)
 };
 
@@ -77,7 +75,7 @@ inline void thresholds(double beta, unsigned long long thr[3]) {
 struct pa_instance {
   pa_host::Layout lay;
   pa::DevPop dev;
-  pa::DevPop* d_pops = nullptr;      // device copy of dev (slot 0) and an overlap partner (slot 1)
+  pa::DevPop* d_pops = nullptr;      // device copy of dev
   pa_host::MetaU32* d_meta = nullptr;
   pa_host::MetaU32 meta{};
   hipStream_t stream = nullptr;
@@ -109,7 +107,6 @@ struct pa_instance {
                                       // resampling step weighs (its ln Q needs it)
   unsigned long long* h_ovl = nullptr;
   unsigned long long* h_lovl = nullptr;  // 3N + 1 link-overlap counts
-  pa_host::MetaU32* h_meta = nullptr;
   unsigned long long* h_gthr = nullptr;  // PA_MODEL_GAUSS16 threshold table staging
   hipEvent_t gthr_copied = nullptr;      // recorded after each copy out of h_gthr
   bool in_batch = false;

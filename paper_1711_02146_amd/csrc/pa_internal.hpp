@@ -35,6 +35,7 @@ constexpr int kMaxL = 16;
 // the neighbour pattern (Gaussian couplings).  With the 8 KB tile image at L = 10, eight such areas leave four
 // workgroups of eight waves (eight waves per SIMD) in a CU's 160 KB.
 constexpr uint32_t kPlaneAreaBytes = 64 * 64;
+constexpr uint32_t kOverlapTiles = 8;  // 64-pair tiles (one wave each) per workgroup of k_overlap
 constexpr uint32_t kLinkCopies = 32;  // partial link-overlap histograms (see launch_link_overlap)
 // Energy models.  kModelPm: J = +-1, the energy word of a replica is U, the
 // number of unsatisfied bonds (E = 2U - 3N).  kModelGauss16: J = k / 16 with
@@ -290,10 +291,13 @@ hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint
                         uint32_t split, uint32_t model, hipStream_t stream);
 hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream);
 hipError_t launch_record(const BatchDev& B, const Group& per_pop, hipStream_t stream);
-// cur_a / cur_b: the two populations' buffers when B carries no per-step parameters
+// overlap histograms of a batch step's pairs (blocks_overlap workgroups each)
 hipError_t launch_overlap(const BatchDev& B, const Group& pairs, const uint32_t* pair_pops,
-                          uint32_t layout, bool post, uint32_t cur_a, uint32_t cur_b,
-                          hipStream_t stream);
+                          uint32_t layout, hipStream_t stream);
+// the same for two instances, their current buffers cur_a and cur_b, into
+// a.ovl_hist (cleared first)
+hipError_t launch_overlap_pair(const DevPop& a, const DevPop& b, uint32_t cur_a, uint32_t cur_b,
+                               hipStream_t stream);
 // energy word of every replica of buffer cur recomputed from its spins: stored
 // (check == false), or compared with the stored word, the number of replicas
 // that differ added to sc->check_bad (check == true)
@@ -347,6 +351,9 @@ hipError_t launch_real_counts(const BatchDev& B, const Group& slots, hipStream_t
 
 // Blocks each population needs in each kind of launch.
 inline uint32_t blocks_hist(uint32_t capacity) { return (capacity + kHistSlots - 1) / kHistSlots; }
+inline uint32_t blocks_overlap(uint32_t capacity) {
+  return (capacity / 64 + kOverlapTiles - 1) / kOverlapTiles;
+}
 inline uint32_t blocks_slots(uint32_t capacity) { return capacity / kBlockCounts; }
 // One block per tile, rounded up to a multiple of 8 so that every population
 // of a launch starts at a block number divisible by the XCD count (the extra

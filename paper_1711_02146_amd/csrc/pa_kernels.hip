@@ -1916,20 +1916,215 @@ __global__ __launch_bounds__(256) void k_record(BatchDev B, Group G) {
   }
 }
 
-// Spin-overlap histogram (Sec. II.A): slot i of population a against slot i
-// of population b; d = differing sites, bin = (128 (N - d) + N) / (2N).
-// Member m of the group is pair k = G.pop[m] (populations pair_pops[2k], pair_pops[2k+1]).
-// One workgroup per 64-pair tile; its kOverlapWaves waves take every
-// kOverlapWaves-th site (more loads in flight than one wave per tile) and
-// their counts are added per pair through LDS.
-constexpr uint32_t kOverlapWaves = 4;
+// ---------------------------------------------------------------------------
+// Counting over sites for 64 pairs at a time.  With lane = site, a lane's words
+// hold one bit per pair; the number of set bits per pair is kept as bit planes
+// (plane k: bit k of the 64 pairs' counts), added with full adders on whole
+// words, first within a lane, then across the lanes of the wave.
+// ---------------------------------------------------------------------------
+typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) U32x2 GlobalU32x2;
+typedef const __attribute__((address_space(1))) U32x4 GlobalU32x4;
 
+struct FullSum {
+  uint32_t s, c;
+};
+__device__ __forceinline__ FullSum full_add(uint32_t a, uint32_t b, uint32_t c) {
+  FullSum r;
+  r.s = xor3_v(a, b, c);
+  r.c = maj3_v(a, b, c);
+  return r;
+}
+
+// p += q (NP planes each), the sum in NP + 1 planes of p.
+template <int NP>
+__device__ __forceinline__ void planes_add(uint32_t* p, const uint32_t* q) {
+  uint32_t c = p[0] & q[0];
+  p[0] ^= q[0];
+#pragma unroll
+  for (int k = 1; k < NP; ++k) {
+    const FullSum f = full_add(p[k], q[k], c);
+    p[k] = f.s;
+    c = f.c;
+  }
+  p[NP] = c;
+}
+
+// p += the same planes of the lane a DPP control pairs this one with.
+template <int NP, int CTRL>
+__device__ __forceinline__ void planes_add_dpp(uint32_t* p) {
+  uint32_t q[NP];
+#pragma unroll
+  for (int k = 0; k < NP; ++k)
+    q[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)p[k], CTRL, 0xF, 0xF, true);
+  planes_add<NP>(p, q);
+}
+
+// The count of this lane's pair: lo and hi are every lane's NP-plane counts of
+// pairs 0..31 and 32..63.  One swap of the wave's halves leaves lanes 0..31
+// with the sums of the first 32 pairs and lanes 32..63 with those of the
+// others (half the planes to carry on); five more additions cover the 32 lanes
+// of a half: across the two rows of 16, then i with 15 - i, 7 - i, i ^ 2 and
+// i ^ 1 within a row, which together reach all 16.
+template <int NP>
+__device__ __forceinline__ uint32_t lane_count(const uint32_t (&lo)[NP], const uint32_t (&hi)[NP]) {
+  uint32_t p[NP + 6], q[NP + 1];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(lo[k], hi[k], false, false);
+    p[k] = r[0];
+    q[k] = r[1];
+  }
+  planes_add<NP>(p, q);
+#pragma unroll
+  for (int k = 0; k < NP + 1; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(p[k], p[k], false, false);
+    p[k] = r[0];
+    q[k] = r[1];
+  }
+  planes_add<NP + 1>(p, q);
+  planes_add_dpp<NP + 2, 0x140>(p);  // row_mirror
+  planes_add_dpp<NP + 3, 0x141>(p);  // row_half_mirror
+  planes_add_dpp<NP + 4, 0x4E>(p);   // quad_perm 2,3,0,1
+  planes_add_dpp<NP + 5, 0xB1>(p);   // quad_perm 1,0,3,2
+  const uint32_t pos = lane_id() & 31u;
+  uint32_t d = 0;
+#pragma unroll
+  for (int k = 0; k < NP + 6; ++k) d |= bit_of(p[k], pos) << k;
+  return d;
+}
+
+// One 32-pair half of the words of eight sites added to a 7-plane count (at
+// most 64 sites per lane: N <= 4096).
+__device__ __forceinline__ void add_eight(uint32_t (&p)[7], const uint32_t (&w)[8]) {
+  const FullSum a = full_add(p[0], w[0], w[1]);
+  const FullSum b = full_add(a.s, w[2], w[3]);
+  const FullSum c = full_add(p[1], a.c, b.c);
+  const FullSum d = full_add(b.s, w[4], w[5]);
+  const FullSum e = full_add(d.s, w[6], w[7]);
+  const FullSum f = full_add(c.s, d.c, e.c);
+  const FullSum g = full_add(p[2], c.c, f.c);
+  p[0] = e.s;
+  p[1] = f.s;
+  p[2] = g.s;
+  uint32_t cy = g.c;
+#pragma unroll
+  for (int k = 3; k < 7; ++k) {
+    const uint32_t n = p[k] & cy;
+    p[k] ^= cy;
+    cy = n;
+  }
+}
+
+// d of this lane's pair in the tile: the number of sites where the two
+// populations' spins differ.  Called by one whole wave.
+//
+// Bit-packed: lane = site, one 8-byte word of each population per site, the
+// differing bits counted in planes (about 350 instructions per 64 pairs at
+// L = 10, where reading the bit of every site and pair takes 5000).  int8: a
+// lane takes 16 replicas of a site per 16-byte load and adds their differing
+// bytes in place (+-1 bytes differ in bit 1), 16 sites per load instruction;
+// `d16` (64 halfwords of LDS, one wave's own) turns the counts back to
+// lane = pair.  Bound by the loads: both overlap histograms of two bit-packed
+// populations at L = 10, R = 5e5 took 678 us (this kernel 429), now 141.
 template <int LAYOUT>
-__global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(BatchDev B, Group G,
-                                                const uint32_t* __restrict__ pair_pops,
-                                                uint32_t post, uint32_t cur_a1, uint32_t cur_b1) {
+__device__ __forceinline__ uint32_t pair_distance(const void* spins_a, const void* spins_b,
+                                                  uint32_t tile, uint32_t N, uint16_t* d16) {
+  const uint32_t lane = lane_id();
+  if constexpr (LAYOUT == 2) {
+    GlobalU32x2* a = (GlobalU32x2*)spins_a + (size_t)tile * N;
+    GlobalU32x2* b = (GlobalU32x2*)spins_b + (size_t)tile * N;
+    uint32_t lo[7] = {}, hi[7] = {};
+    for (uint32_t c0 = 0; c0 < N; c0 += 512) {
+      uint32_t xl[8], xh[8];
+#pragma unroll
+      for (uint32_t i = 0; i < 8; ++i) {
+        const uint32_t cm = c0 + 64 * i + lane;
+        xl[i] = xh[i] = 0;
+        if (cm < N) {
+          const U32x2 x = a[cm] ^ b[cm];
+          xl[i] = x[0];
+          xh[i] = x[1];
+        }
+      }
+      add_eight(lo, xl);
+      add_eight(hi, xh);
+    }
+    return lane_count<7>(lo, hi);
+  } else {
+    // lane: replicas 16 (lane & 3) .. + 15 of sites lane >> 2, + 16, + 32, ...
+    GlobalU32x4* a = (GlobalU32x4*)spins_a + (size_t)tile * N * 4 + lane;
+    GlobalU32x4* b = (GlobalU32x4*)spins_b + (size_t)tile * N * 4 + lane;
+    const uint32_t sites = (N - (lane >> 2) + 15) / 16;  // N >= 64
+    // per replica 2 x the count: bytes for up to 64 sites, then 16-bit halves
+    uint32_t even[4] = {}, odd[4] = {};
+    for (uint32_t s0 = 0; s0 < sites; s0 += 64) {
+      U32x4 acc = {0, 0, 0, 0};
+      const uint32_t s1 = min(sites, s0 + 64);
+#pragma unroll 8
+      for (uint32_t s = s0; s < s1; ++s) acc += (a[64 * s] ^ b[64 * s]) & 0x02020202u;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        even[k] += acc[k] & 0x00FF00FFu;
+        odd[k] += (acc[k] >> 8) & 0x00FF00FFu;
+      }
+    }
+#pragma unroll
+    for (int off = 4; off < 64; off <<= 1)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        even[k] += __shfl_xor(even[k], off, kWave);
+        odd[k] += __shfl_xor(odd[k], off, kWave);
+      }
+    if (lane < 4) {
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        d16[16 * lane + 4 * k] = (uint16_t)(even[k] & 0xFFFFu);
+        d16[16 * lane + 4 * k + 1] = (uint16_t)(odd[k] & 0xFFFFu);
+        d16[16 * lane + 4 * k + 2] = (uint16_t)(even[k] >> 16);
+        d16[16 * lane + 4 * k + 3] = (uint16_t)(odd[k] >> 16);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    return (uint32_t)d16[lane] >> 1;
+  }
+}
+
+// Spin-overlap histogram (Sec. II.A): slot i of population a against slot i
+// of population b; d = differing sites, bin = (128 (N - d) + N) / (2N).  One
+// wave per 64-pair tile, kOverlapTiles tiles per workgroup, which count in one
+// LDS histogram (eight times fewer global atomic adds than a workgroup per
+// tile).
+template <int LAYOUT>
+__device__ __forceinline__ void overlap_tiles(const DevPop& A, const DevPop& Bp, uint32_t cur_a,
+                                              uint32_t cur_b, uint32_t block,
+                                              unsigned long long* out) {
   __shared__ uint32_t hb[65];
-  __shared__ uint32_t dpart[kOverlapWaves][64];
+  __shared__ uint16_t d16[kOverlapTiles * 64];
+  const uint32_t part = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const uint32_t tile = block * kOverlapTiles + part, lane = lane_id();
+  const uint32_t n = min(A.sc->R_tilde, Bp.sc->R_tilde), N = A.N;
+  if (block * kOverlapTiles * 64 >= n) return;
+  if (threadIdx.x < 65) hb[threadIdx.x] = 0;
+  __syncthreads();
+  if (tile * 64 < n) {
+    const uint32_t d = pair_distance<LAYOUT>(pick(A.spins, cur_a), pick(Bp.spins, cur_b), tile, N,
+                                             d16 + 64 * part);
+    if (tile * 64 + lane < n) atomicAdd(&hb[(128u * (N - d) + N) / (2u * N)], 1u);
+  }
+  __syncthreads();
+  if (threadIdx.x < 65 && hb[threadIdx.x])
+    atomicAdd(&out[threadIdx.x], (unsigned long long)hb[threadIdx.x]);
+}
+
+// Pairs of a batch step: member m of the group is pair k = G.pop[m]
+// (populations pair_pops[2k], pair_pops[2k+1]), after the step's sweep.
+template <int LAYOUT>
+__global__ __launch_bounds__(64 * kOverlapTiles) void k_overlap(
+    BatchDev B, Group G, const uint32_t* __restrict__ pair_pops) {
   const Member m = member_of(G);
   const uint32_t k = m.pop;  // pair index
   const uint32_t ia = __builtin_amdgcn_readfirstlane(pair_pops[2 * k]);
@@ -1937,134 +2132,104 @@ __global__ __launch_bounds__(64 * kOverlapWaves) void k_overlap(BatchDev B, Grou
   const DevPop A = B.pops[ia];
   const DevPop Bp = B.pops[ib];
   if (A.sc->dead || Bp.sc->dead) return;
-  // batch steps carry each population's buffer; a call on two instances passes them
-  const uint32_t base_a = B.steps ? step_of(B, ia).cur : cur_a1;
-  const uint32_t base_b = B.steps ? step_of(B, ib).cur : cur_b1;
-  const uint32_t cur_a = post ? base_a ^ 1u : base_a, cur_b = post ? base_b ^ 1u : base_b;
-  unsigned long long* out =
-      B.qhist ? B.qhist + ((size_t)step_index(B) * B.n_pairs + k) * 65 : A.ovl_hist;
-  const uint32_t tile = m.lb;
-  const uint32_t lane = lane_id();
-  const uint32_t part = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
-  const uint32_t n = min(A.sc->R_tilde, Bp.sc->R_tilde);
-  if (tile * 64 >= n) return;
-  for (uint32_t b = threadIdx.x; b < 65; b += 64 * kOverlapWaves) hb[b] = 0;
-  const uint32_t i = tile * 64 + lane;
-  const uint32_t N = A.N;
-  uint32_t d = 0;
-  if (LAYOUT == 2) {
-    const unsigned long long* a = static_cast<const unsigned long long*>(pick(A.spins, cur_a)) +
-                                  (size_t)tile * N;
-    const unsigned long long* b = static_cast<const unsigned long long*>(pick(Bp.spins, cur_b)) +
-                                  (size_t)tile * N;
-#pragma unroll 8
-    for (uint32_t cm = part; cm < N; cm += kOverlapWaves)
-      d += (uint32_t)((a[cm] ^ b[cm]) >> lane) & 1u;
-  } else {
-    const int8_t* a = static_cast<const int8_t*>(pick(A.spins, cur_a)) + (size_t)tile * N * 64 + lane;
-    const int8_t* b = static_cast<const int8_t*>(pick(Bp.spins, cur_b)) + (size_t)tile * N * 64 + lane;
-#pragma unroll 8
-    for (uint32_t cm = part; cm < N; cm += kOverlapWaves) d += a[64 * (size_t)cm] != b[64 * (size_t)cm];
-  }
-  dpart[part][lane] = d;
-  __syncthreads();
-  if (part == 0) {
-    d = 0;
-#pragma unroll
-    for (uint32_t w = 0; w < kOverlapWaves; ++w) d += dpart[w][lane];
-    if (i < n) atomicAdd(&hb[(128u * (N - d) + N) / (2u * N)], 1u);
-  }
-  __syncthreads();
-  for (uint32_t b = threadIdx.x; b < 65; b += 64 * kOverlapWaves)
-    if (hb[b]) atomicAdd(&out[b], (unsigned long long)hb[b]);
+  overlap_tiles<LAYOUT>(A, Bp, step_of(B, ia).cur ^ 1u, step_of(B, ib).cur ^ 1u, m.lb,
+                        B.qhist + ((size_t)step_index(B) * B.n_pairs + k) * 65);
+}
+
+// A call on two instances: their descriptors travel with the launch.
+template <int LAYOUT>
+__global__ __launch_bounds__(64 * kOverlapTiles) void k_overlap_pair(DevPop A, DevPop Bp,
+                                                                     uint32_t cur_a,
+                                                                     uint32_t cur_b) {
+  if (A.sc->dead || Bp.sc->dead) return;
+  overlap_tiles<LAYOUT>(A, Bp, cur_a, cur_b, blockIdx.x, A.ovl_hist);
+}
+
+// Bit 1 of the four bytes of x (0 or 1 each) as bits 0..3.
+__device__ __forceinline__ uint32_t bytes_to_bits(uint32_t x) {
+  return (((x >> 1) & 0x01010101u) * 0x10204080u) >> 28;
 }
 
 // Link-overlap histogram (Sec. II.A): slot i of population a against slot i
 // of population b, one 64-pair tile per wave.  With x_n = s^a_n s^b_n a bond
 // <n,m> contributes x_n x_m, so only the bonds whose ends differ in x count:
 // D = their number, q_l = 1 - 2 D / (3N), hist[D] += 1 per pair.  The tile's x
-// words go to LDS (colour-major, 64 pairs per site, 8N bytes); each lane then
-// reads the half word holding its pair.  For even L every bond joins a
-// colour-0 site to a colour-1 site, so the walk over the six bonds of every
-// colour-0 site counts each bond once.
-//
-// The colour-0 sites of row (y, z) sit at x = 2q + P, P = (y + z) & 1; their
-// +x and -x neighbours are ranks (q + P) and (q + P - 1) mod L/2 of the
-// colour-1 row (y, z), their y and z neighbours rank q of the colour-1 rows
-// (y +- 1, z) and (y, z +- 1).  Each bond costs one masked XOR (the lane's
-// bit of own ^ neighbour) and one popcount-accumulate.
-template <int L, int P>
-__device__ __forceinline__ uint32_t link_row(const uint32_t* own, const uint32_t* xr,
-                                             const uint32_t* py, const uint32_t* my,
-                                             const uint32_t* pz, const uint32_t* mz, uint32_t m,
-                                             uint32_t d) {
-  constexpr int H = L / 2;
-#pragma unroll
-  for (int q = 0; q < H; ++q) {
-    const uint32_t o = own[2 * q];
-    const int qp = (q + P) % H, qm = (q + P + H - 1) % H;
-    d += __builtin_popcount((o ^ xr[2 * qp]) & m);
-    d += __builtin_popcount((o ^ xr[2 * qm]) & m);
-    d += __builtin_popcount((o ^ py[2 * q]) & m);
-    d += __builtin_popcount((o ^ my[2 * q]) & m);
-    d += __builtin_popcount((o ^ pz[2 * q]) & m);
-    d += __builtin_popcount((o ^ mz[2 * q]) & m);
-  }
-  return d;
-}
-
+// words go to LDS (colour-major, 64 pairs per site, 8N bytes).  For even L
+// every bond joins a colour-0 site to a colour-1 site, so the six bonds of
+// every colour-0 site cover each bond once: lane = colour-0 site, the six
+// words own ^ neighbour added into planes (as the +-J colour pass does), the
+// sites of a lane and then the lanes added in planes (see lane_count).  At L = 10 about 900 instructions per 64 pairs, where a masked XOR
+// and a population count per bond and pair take 6000 (163 us at R = 5e5
+// before); what is left is bound by the loads.
 template <int LAYOUT, int L>
 __global__ __launch_bounds__(64) void k_link_overlap(DevPop A, DevPop Bp, uint32_t cur_a,
                                                      uint32_t cur_b,
                                                      uint32_t* __restrict__ part) {
-  constexpr uint32_t H = L / 2, N = L * L * L;
-  __shared__ uint32_t xs[2 * N];  // site cm: words 2 cm (pairs 0..31), 2 cm + 1 (32..63)
+  constexpr uint32_t N = L * L * L;
+  __shared__ uint2 xs[N];  // site cm: pairs 0..31 and 32..63
   const uint32_t tile = blockIdx.x;
   const uint32_t lane = lane_id();
   const uint32_t n = min(A.sc->R_tilde, Bp.sc->R_tilde);
   if (tile * 64 >= n) return;
-  if (LAYOUT == 2) {
-    const unsigned long long* a = static_cast<const unsigned long long*>(pick(A.spins, cur_a)) +
-                                  (size_t)tile * N;
-    const unsigned long long* b = static_cast<const unsigned long long*>(pick(Bp.spins, cur_b)) +
-                                  (size_t)tile * N;
+  if constexpr (LAYOUT == 2) {
+    typedef const __attribute__((address_space(1))) unsigned long long GlobalU64;
+    GlobalU64* a = (GlobalU64*)pick(A.spins, cur_a) + (size_t)tile * N;
+    GlobalU64* b = (GlobalU64*)pick(Bp.spins, cur_b) + (size_t)tile * N;
+#pragma unroll 8
     for (uint32_t cm = lane; cm < N; cm += 64) {
       const unsigned long long x = a[cm] ^ b[cm];
-      xs[2 * cm] = (uint32_t)x;
-      xs[2 * cm + 1] = (uint32_t)(x >> 32);
+      xs[cm] = make_uint2((uint32_t)x, (uint32_t)(x >> 32));
     }
   } else {
-    const int8_t* a = static_cast<const int8_t*>(pick(A.spins, cur_a)) + (size_t)tile * N * 64 + lane;
-    const int8_t* b = static_cast<const int8_t*>(pick(Bp.spins, cur_b)) + (size_t)tile * N * 64 + lane;
-#pragma unroll 8
-    for (uint32_t cm = 0; cm < N; ++cm) {
-      const unsigned long long x = __ballot(a[64 * (size_t)cm] != b[64 * (size_t)cm]);
-      if (lane == 0) {
-        xs[2 * cm] = (uint32_t)x;
-        xs[2 * cm + 1] = (uint32_t)(x >> 32);
-      }
+    // 16 replicas of a site per lane and load, 16 sites per instruction
+    GlobalU32x4* a = (GlobalU32x4*)pick(A.spins, cur_a) + (size_t)tile * N * 4;
+    GlobalU32x4* b = (GlobalU32x4*)pick(Bp.spins, cur_b) + (size_t)tile * N * 4;
+    uint16_t* const x16 = reinterpret_cast<uint16_t*>(xs);
+#pragma unroll 4
+    for (uint32_t i = lane; i < 4 * N; i += 64) {
+      const U32x4 x = a[i] ^ b[i];
+      x16[i] = (uint16_t)(bytes_to_bits(x[0]) | bytes_to_bits(x[1]) << 4 |
+                          bytes_to_bits(x[2]) << 8 | bytes_to_bits(x[3]) << 12);
     }
   }
   __syncthreads();
-  const uint32_t* xh = xs + (lane >> 5);
-  const uint32_t m = 1u << (lane & 31u);
-  uint32_t d = 0;
-  for (uint32_t z = 0; z < (uint32_t)L; ++z) {
-    const uint32_t zp = z + 1 == (uint32_t)L ? 0 : z + 1, zm = z == 0 ? L - 1 : z - 1;
-    for (uint32_t y = 0; y < (uint32_t)L; ++y) {
-      const uint32_t yp = y + 1 == (uint32_t)L ? 0 : y + 1, ym = y == 0 ? L - 1 : y - 1;
-      const uint32_t* own = xh + whole_s(2 * H * (y + L * z));
-      const uint32_t* xr = xh + whole_s(2 * (N / 2 + H * (y + L * z)));
-      const uint32_t* py = xh + whole_s(2 * (N / 2 + H * (yp + L * z)));
-      const uint32_t* my = xh + whole_s(2 * (N / 2 + H * (ym + L * z)));
-      const uint32_t* pz = xh + whole_s(2 * (N / 2 + H * (y + L * zp)));
-      const uint32_t* mz = xh + whole_s(2 * (N / 2 + H * (y + L * zm)));
-      if ((y + z) & 1u)
-        d = link_row<L, 1>(own, xr, py, my, pz, mz, m, d);
-      else
-        d = link_row<L, 0>(own, xr, py, my, pz, mz, m, d);
+  // six bonds for each of a lane's sites: at most 6 ceil(N / 128) < 2^NP
+  constexpr int NP = L >= 14 ? 8 : L == 12 ? 7 : L == 10 ? 6 : L >= 6 ? 5 : 3;
+  static_assert(6 * ((N / 2 + 63) / 64) < (1u << NP), "the planes hold a lane's count");
+  uint32_t lo[NP] = {}, hi[NP] = {};
+  const uint32_t none[6] = {0, 0, 0, 0, 0, 0};
+#pragma unroll 2
+  for (uint32_t cm = lane; cm < N / 2; cm += 64) {
+    const SiteWords e = load_site(A.sites, cm);
+    const uint2 o = xs[cm];
+    uint32_t nl[6], nh[6];
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const uint2 v = xs[e.nb[k]];
+      nl[k] = v.x;
+      nh[k] = v.y;
+    }
+    const NuPlanes pl = nu_planes(o.x, nl, none), ph = nu_planes(o.y, nh, none);
+    const uint32_t ql[3] = {pl.p0, pl.p1, pl.p2}, qh[3] = {ph.p0, ph.p1, ph.p2};
+    uint32_t cl = 0, ch = 0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const FullSum fl = full_add(lo[k], ql[k], cl), fh = full_add(hi[k], qh[k], ch);
+      lo[k] = fl.s;
+      cl = fl.c;
+      hi[k] = fh.s;
+      ch = fh.c;
+    }
+#pragma unroll
+    for (int k = 3; k < NP; ++k) {
+      const uint32_t tl = lo[k] & cl, th = hi[k] & ch;
+      lo[k] ^= cl;
+      hi[k] ^= ch;
+      cl = tl;
+      ch = th;
     }
   }
+  const uint32_t d = lane_count<NP>(lo, hi);
   // each tile counts into copy tile mod kLinkCopies of the histogram, so that
   // concurrent waves rarely update the same word; k_link_reduce sums the copies
   if (tile * 64 + lane < n) atomicAdd(&part[(tile % kLinkCopies) * (3 * N + 1) + d], 1u);
@@ -2077,6 +2242,7 @@ __global__ __launch_bounds__(256) void k_link_reduce(const uint32_t* __restrict_
   const uint32_t b = blockIdx.x * 256 + threadIdx.x;
   if (b >= nbins) return;
   unsigned long long acc = 0;
+#pragma unroll
   for (uint32_t k = 0; k < kLinkCopies; ++k) acc += part[(size_t)k * nbins + b];
   hist[b] = acc;
 }
@@ -2391,15 +2557,27 @@ hipError_t launch_record(const BatchDev& B, const Group& g, hipStream_t stream) 
 }
 
 hipError_t launch_overlap(const BatchDev& B, const Group& g, const uint32_t* pair_pops,
-                          uint32_t layout, bool post, uint32_t cur_a, uint32_t cur_b,
-                          hipStream_t stream) {
+                          uint32_t layout, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
   if (layout == 2)
-    hipLaunchKernelGGL(k_overlap<2>, dim3(g.blocks), dim3(64 * kOverlapWaves), 0, stream, B, g, pair_pops,
-                       post ? 1u : 0u, cur_a, cur_b);
+    hipLaunchKernelGGL(k_overlap<2>, dim3(g.blocks), dim3(64 * kOverlapTiles), 0, stream, B, g,
+                       pair_pops);
   else
-    hipLaunchKernelGGL(k_overlap<1>, dim3(g.blocks), dim3(64 * kOverlapWaves), 0, stream, B, g, pair_pops,
-                       post ? 1u : 0u, cur_a, cur_b);
+    hipLaunchKernelGGL(k_overlap<1>, dim3(g.blocks), dim3(64 * kOverlapTiles), 0, stream, B, g,
+                       pair_pops);
+  return hipGetLastError();
+}
+
+hipError_t launch_overlap_pair(const DevPop& a, const DevPop& b, uint32_t cur_a, uint32_t cur_b,
+                               hipStream_t stream) {
+  if (a.N != b.N || a.layout != b.layout) return hipErrorInvalidValue;
+  const uint32_t blocks = blocks_overlap(std::min(a.capacity, b.capacity));
+  if (a.layout == 2)
+    hipLaunchKernelGGL(k_overlap_pair<2>, dim3(blocks), dim3(64 * kOverlapTiles), 0, stream, a, b,
+                       cur_a, cur_b);
+  else
+    hipLaunchKernelGGL(k_overlap_pair<1>, dim3(blocks), dim3(64 * kOverlapTiles), 0, stream, a, b,
+                       cur_a, cur_b);
   return hipGetLastError();
 }
 
