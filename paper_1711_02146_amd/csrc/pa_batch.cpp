@@ -265,8 +265,9 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
     for (uint32_t p : kv.second) tiles += (pops[p]->dev.R + 63) / 64;
     const uint32_t split =
         pa::sweep_split_for(pa::kModelPm, kv.first.first, kv.first.second, tiles);
+    const uint32_t per_block = pa::sweep_tiles(pa::kModelPm, kv.first.second, split);
     std::vector<uint32_t> nb;
-    for (uint32_t p : kv.second) nb.push_back(pa::blocks_sweep(pops[p]->dev.capacity));
+    for (uint32_t p : kv.second) nb.push_back(pa::blocks_sweep(pops[p]->dev.capacity, per_block));
     b->g_sweep.push_back({kv.first.first, kv.first.second, split, add_group(kv.second, nb)});
   }
   for (uint32_t layout : {(uint32_t)PA_LAYOUT_INT8, (uint32_t)PA_LAYOUT_BITPACK64}) {

@@ -303,6 +303,15 @@ pa::PopStep plain_step(uint32_t cur) {
   return ps;
 }
 
+// The workgroups of a sweep launch of one instance in the form `split` (the
+// start table is made for one tile per workgroup; with one member it only says
+// that every block is the member's).
+pa::Group sweep_group(const pa_instance* in, uint32_t split) {
+  return group_of(in, in->d_meta->tiles,
+                  pa::blocks_sweep(in->dev.capacity,
+                                   pa::sweep_tiles(in->dev.model, in->dev.L, split)));
+}
+
 // Sweep launch of one instance (its size after any pending copy sets the
 // waves per tile).
 hipError_t launch_sweep_of(pa_instance* in, const pa::PopStep& ps) {
@@ -311,8 +320,8 @@ hipError_t launch_sweep_of(pa_instance* in, const pa::PopStep& ps) {
   const bool timed = in->sweep_ev[0] != nullptr;
   hipError_t e = timed ? hipEventRecord(in->sweep_ev[0], in->stream) : hipSuccess;
   if (e != hipSuccess) return e;
-  e = pa::launch_sweep(one_set(in, ps), group_of(in, in->d_meta->tiles, in->meta.tiles[1]),
-                       in->dev.layout, in->dev.L, split, in->dev.model, in->stream);
+  e = pa::launch_sweep(one_set(in, ps), sweep_group(in, split), in->dev.layout, in->dev.L, split,
+                       in->dev.model, in->stream);
   if (e != hipSuccess || !timed) return e;
   in->sweep_timed = true;
   return hipEventRecord(in->sweep_ev[1], in->stream);
@@ -1227,6 +1236,7 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
   P.table = reinterpret_cast<pa::TableEntry*>(w + l.off_table);
   P.sites = reinterpret_cast<const SiteEntry*>(w + l.off_sites);
   P.psites = reinterpret_cast<const pa::PlaneSite*>(w + l.off_psites);
+  P.pmsites = reinterpret_cast<const pa::PmSite*>(w + l.off_psites);
   P.cm_of_site = reinterpret_cast<const uint16_t*>(w + l.off_cm);
   P.rowj = reinterpret_cast<const unsigned long long*>(w + l.off_rowj);
   P.ovl_hist = reinterpret_cast<unsigned long long*>(w + l.off_ovl);
@@ -1251,7 +1261,7 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
   mt.perpop[0] = 0; mt.perpop[1] = 1;
   mt.slots[0] = 0; mt.slots[1] = pa::blocks_slots(l.capacity);
   mt.hist[0] = 0; mt.hist[1] = pa::blocks_hist(l.capacity);
-  mt.tiles[0] = 0; mt.tiles[1] = pa::blocks_sweep(l.capacity);
+  mt.tiles[0] = 0; mt.tiles[1] = pa::blocks_sweep(l.capacity, 1);
   mt.etiles[0] = 0; mt.etiles[1] = l.capacity / 64;
   mt.rsum[0] = 0; mt.rsum[1] = std::min(pa::blocks_slots(l.capacity), pa::kRealSumBlocks);
 
@@ -1283,14 +1293,27 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
        hipEventRecord(in->gthr_copied, in->stream) != hipSuccess))
     return fail(PA_EDEVICE);
 
-  // phase 1 of the +-J colour pass reads each site's neighbours at the LDS
-  // addresses of their words in the tile image
+  // phase 1 of the colour passes reads each site's neighbours in the LDS tile
+  // image: +-J by their offset in it, Gaussian models by LDS address
   std::vector<pa::PlaneSite> psites(l.N);
-  for (uint32_t cm = 0; cm < l.N; ++cm) {
-    pa::PlaneSite& q = psites[cm];
-    for (int k = 0; k < 6; ++k) q.nb8[k] = pa::kTileLdsBase + 8u * in->sites[cm].nb[k];
-    q.jneg = in->sites[cm].jneg;
-    q.pad = 0;
+  if (l.model == PA_MODEL_PM) {
+    pa::PmSite* const q = reinterpret_cast<pa::PmSite*>(psites.data());
+    for (uint32_t cm = 0; cm < l.N; ++cm)
+      for (uint32_t h = 0; h < 2; ++h) {
+        pa::PmSite& e = q[8 * (cm >> 2) + 4 * h + (cm & 3u)];
+        for (int k = 0; k < 6; ++k) {
+          const uint32_t n = in->sites[cm].nb[k];
+          e.nb[k] = (uint16_t)(8u * ((n & 3u) * (l.N / 4) + (n >> 2)) + 4u * h);
+        }
+        e.jneg = in->sites[cm].jneg;
+      }
+  } else {
+    for (uint32_t cm = 0; cm < l.N; ++cm) {
+      pa::PlaneSite& q = psites[cm];
+      for (int k = 0; k < 6; ++k) q.nb8[k] = pa::kTileLdsBase + 8u * in->sites[cm].nb[k];
+      q.jneg = in->sites[cm].jneg;
+      q.pad = 0;
+    }
   }
   // tables and scalars (synchronous copies from pageable host memory)
   DevScalars sc{};
@@ -1766,10 +1789,10 @@ int pa_autotune_sweep(pa_instance* in, double beta, uint32_t n_sweeps, uint32_t 
   }
   int rc = PA_OK;
   const pa::BatchDev B = one_set(in, ps);
-  const pa::Group g = group_of(in, in->d_meta->tiles, in->meta.tiles[1]);
   auto launch = [&](uint32_t split) {
-    return pa::launch_sweep(B, g, in->dev.layout, in->dev.L, split, in->dev.model, in->stream) ==
-           hipSuccess;
+    const uint32_t form = pa::sweep_form(in->dev.model, in->dev.L, split, tiles);
+    return pa::launch_sweep(B, sweep_group(in, form), in->dev.layout, in->dev.L, form,
+                            in->dev.model, in->stream) == hipSuccess;
   };
   // two untimed launches of each form (clocks and caches settle), then the
   // timed launches alternate between the forms so that drift hits both alike

@@ -91,6 +91,30 @@ struct PlaneSite {
 };
 static_assert(sizeof(PlaneSite) == 32, "PlaneSite must be 32 bytes");
 
+// The +-J sweep (k_sweep_pm): LDS address of the tile image, after the 4 KB
+// threshold table, and the bytes of a wave's plane area (32 groups of four
+// sites x 64 replicas, one byte each).
+constexpr uint32_t kPmImage = 4096;
+constexpr uint32_t kPmPlaneBytes = 32 * 64;
+// Forms of the +-J sweep (see PmShape): 4 or 8 waves on one tile, or, for L <= 8,
+// four waves on several tiles: waves and tiles per workgroup.
+constexpr uint32_t kPmPacked = 1;
+__host__ __device__ constexpr uint32_t pm_waves(uint32_t split) { return split == 8 ? 8 : 4; }
+__host__ __device__ constexpr uint32_t pm_tiles(uint32_t L, uint32_t split) {
+  return split != kPmPacked ? 1 : L <= 6 ? 4 : L == 8 ? 2 : 1;
+}
+
+// A site for one 32-replica half of a lane in phase 1 of the +-J colour pass:
+// the byte offsets of the six neighbours' words of that half in the tile's
+// image and the coupling bits.  The table holds, for each group of four consecutive sites, the four
+// sites for the low half, then for the high half: a lane reads 64 bytes in a row.
+struct PmSite {
+  uint16_t nb[6];
+  uint32_t jneg;
+};
+static_assert(sizeof(PmSite) == 16 && 2 * sizeof(PmSite) == sizeof(PlaneSite),
+              "a site takes 32 bytes in either table");
+
 // Device-resident scalars of one population.
 struct DevScalars {
   uint32_t R_tilde;       // size of the current population
@@ -177,7 +201,9 @@ struct DevPop {
   uint32_t* hist;               // n_levels
   struct TableEntry* table;     // n_levels: the resampling table by energy level
   const SiteEntry* sites;       // N entries, colour-major
-  const PlaneSite* psites;      // N entries, colour-major (phase 1 of the colour passes)
+  const PlaneSite* psites;      // Gaussian models: N entries, colour-major (phase 1 of the colour
+                                // passes)
+  const PmSite* pmsites;        // kModelPm, in their place: 2 N entries [N / 4][2][4]
   const uint16_t* cm_of_site;   // N entries: lexicographic site -> colour-major index
   const unsigned long long* rowj;  // 2 L^2 row words: bit 6q + k set iff the bond from
                                    // site q of row (colour, y, z) to neighbour k is -1
@@ -285,8 +311,9 @@ hipError_t launch_scan(const BatchDev& B, const Group& per_pop, hipStream_t stre
 hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream);
 // k_scan and k_scatter of one population in one launch (g: its slot blocks)
 hipError_t launch_scan_scatter(const BatchDev& B, const Group& g, hipStream_t stream);
-// sweep launch over the populations of one (layout, L, model) group: one tile
-// per workgroup of `split` (4 or 8) waves; g's blocks are blocks_sweep(capacity)
+// sweep launch over the populations of one (layout, L, model) group in the form
+// `split` (4 or 8 waves per workgroup); g's blocks are blocks_sweep(capacity,
+// sweep_tiles(model, L, split))
 hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint32_t L,
                         uint32_t split, uint32_t model, hipStream_t stream);
 hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream);
@@ -355,23 +382,49 @@ inline uint32_t blocks_overlap(uint32_t capacity) {
   return (capacity / 64 + kOverlapTiles - 1) / kOverlapTiles;
 }
 inline uint32_t blocks_slots(uint32_t capacity) { return capacity / kBlockCounts; }
-// One block per tile, rounded up to a multiple of 8 so that every population
-// of a launch starts at a block number divisible by the XCD count (the extra
-// blocks find no replicas and leave).
-inline uint32_t blocks_sweep(uint32_t capacity) { return (capacity / 64 + 7) / 8 * 8; }
-// Waves per tile of a sweep launch over `tiles` tiles of linear size L, from
-// timings on MI355X (both layouts, beta = 1, 10 sweeps; the same two-phase
-// colour pass for every coupling model): eight waves from L = 10 up, and on
-// smaller lattices while the launch is too small to fill the chip with four
-// (fewer than 256 (L - 2) tiles: 512 at L = 4, 1024 at L = 6, 1536 at L = 8);
-// four otherwise, where more resident tiles per CU pay (L = 4, 4096 tiles:
-// 0.13 against 0.19 ms).
+// One block per `per_block` tiles, rounded up to a multiple of 8 so that every
+// population of a launch starts at a block number divisible by the XCD count
+// (the extra blocks find no replicas and leave).
+inline uint32_t blocks_sweep(uint32_t capacity, uint32_t per_block) {
+  return ((capacity / 64 + per_block - 1) / per_block + 7) / 8 * 8;
+}
+// Tiles per workgroup of a sweep launch.
+inline uint32_t sweep_tiles(uint32_t model, uint32_t L, uint32_t split) {
+  return model == kModelPm ? pm_tiles(L, split) : 1;
+}
+// Waves per workgroup of a sweep launch over `tiles` tiles of linear size L, from
+// timings on MI355X (10 sweeps, beta = 1).
+// +-J: eight waves on a tile while the launch leaves the chip idle (ms per
+// launch with 8 / 4 waves: L = 4, 313 tiles 0.036 / 0.047, 782 tiles 0.059 /
+// 0.044; L = 8, 157 tiles 0.059 / 0.070, 313 tiles 0.087 / 0.087; L = 10, 313
+// tiles 0.140 / 0.152, 782 tiles 0.247 / 0.243) and from L = 12 up, where eight
+// waves still have a full chunk each (L = 12, 3125 tiles 1.152 / 1.175; L = 16,
+// 1563 tiles 1.52 / 1.92); at L = 6 four are never slower (157 tiles 0.046 /
+// 0.046, 1563 tiles 0.186 / 0.132).
+// Gaussian models: eight from L = 10 up, and on smaller lattices while the launch
+// is too small to fill the chip with four (fewer than 256 (L - 2) tiles: 512 at
+// L = 4, 1024 at L = 6, 1536 at L = 8); four otherwise, where more resident tiles
+// per CU pay.
 inline uint32_t sweep_split_default(uint32_t model, uint32_t L, uint64_t tiles) {
-  (void)model;
+  if (model == kModelPm) {
+    const uint64_t few = L == 4 ? 512 : L == 6 ? 0 : L == 8 ? 256 : 768;
+    return L >= 12 || tiles < few ? 8u : 4u;
+  }
   return (L >= 10 || tiles < 256ull * (L - 2)) ? 8u : 4u;
 }
-// The split a launch uses: the autotuner's choice for (model, layout, L, size
-// class of `tiles`) when one was measured in this process, else the default (pa_tune.cpp).
+// The kernel form of a launch with `split` waves per workgroup: +-J on four waves
+// packs several tiles per workgroup where there are enough of them (ms per
+// launch packed / one tile per workgroup: L = 4, 313 tiles 0.044 / 0.047, 7813
+// tiles 0.157 / 0.333; L = 6, 782 tiles 0.104 / 0.086, 1563 tiles 0.128 / 0.132,
+// 7813 tiles 0.386 / 0.498; L = 8, 1563 tiles 0.240 / 0.219, 3125 tiles 0.384 /
+// 0.382, 7813 tiles 0.824 / 0.873).
+inline uint32_t sweep_form(uint32_t model, uint32_t L, uint32_t split, uint64_t tiles) {
+  const uint64_t enough = L == 4 ? 0 : L == 6 ? 1500 : 3200;
+  return model == kModelPm && split == 4 && L <= 8 && tiles >= enough ? kPmPacked : split;
+}
+// The form a launch uses: sweep_form of the autotuner's choice for (model,
+// layout, L, size class of `tiles`) when one was measured in this process, else
+// of the default (pa_tune.cpp).
 uint32_t sweep_split_for(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles);
 void sweep_split_record(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles,
                         uint32_t split);

@@ -42,6 +42,13 @@ __device__ __forceinline__ uint32_t xor3_s(uint32_t a, uint32_t b, uint32_t c) {
   return r;
 }
 
+// the same with all three in vector registers
+__device__ __forceinline__ uint32_t xor3_v(uint32_t a, uint32_t b, uint32_t c) {
+  uint32_t r;
+  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 __device__ __forceinline__ Words4 philox10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                            uint32_t k0, uint32_t k1) {
 #pragma unroll
@@ -172,14 +179,27 @@ __device__ uint32_t tile_energy(const uint32_t* lds, const SiteEntry* __restrict
 // round 1 and the slot half of round 2 are computed once per lane; each call
 // then costs two XORs for round 2 and four instructions per round for rounds
 // 3..10 (two v_mad_u64_u32, two XORs).
+//
+// The keys of rounds 3..10 are held in vector registers: a three-input XOR of
+// vector registers issues in half the time of one that reads a scalar register
+// (67 against 38 T lane-instructions/s measured on MI355X), and the draws alone
+// go from 4.04e12 to 4.73e12 per second.
 struct MetPhilox {
   uint32_t x2, x3;    // round-1 words that depend on slot only
   uint32_t p2hi, p2lo;  // round-2 product of the slot half
   uint32_t k0, k1;    // key (seed)
+  uint32_t r0[8], r1[8];  // keys of rounds 3..10 (r1[0] is folded into a uniform word)
 
   __device__ __forceinline__ void init(uint32_t slot, uint32_t key0, uint32_t key1) {
     k0 = key0;
     k1 = key1;
+#pragma unroll
+    for (uint32_t r = 0; r < 8; ++r) {
+      // (written by asm, so that the compiler keeps the copies rather than the
+      // scalar sums they come from)
+      asm("v_mov_b32 %0, %1" : "=v"(r0[r]) : "s"(key0 + (r + 2u) * 0x9E3779B9u));
+      if (r > 0) asm("v_mov_b32 %0, %1" : "=v"(r1[r]) : "s"(key1 + (r + 2u) * 0xBB67AE85u));
+    }
     const uint64_t pa = (uint64_t)0xD2511F53u * slot;
     x2 = (uint32_t)(pa >> 32) ^ kTagMet ^ key1;
     x3 = (uint32_t)pa;
@@ -200,26 +220,21 @@ struct MetPhilox {
     uint32_t c1 = p2lo;
     uint32_t c2 = x3 ^ ((uint32_t)(b >> 32) ^ r2k1);
     uint32_t c3 = (uint32_t)b;  // uniform
-    uint32_t q0 = k0 + 2u * 0x9E3779B9u, q1 = k1 + 2u * 0xBB67AE85u;
     // round 3: c3 is uniform, fold it into the key word
     {
       const uint64_t pa = (uint64_t)0xD2511F53u * c0;
       const uint64_t pb = (uint64_t)0xCD9E8D57u * c2;
-      const uint32_t n0 = xor3_s((uint32_t)(pb >> 32), c1, q0);
-      const uint32_t n2 = (uint32_t)(pa >> 32) ^ (c3 ^ q1);
+      const uint32_t n0 = xor3_v((uint32_t)(pb >> 32), c1, r0[0]);
+      const uint32_t n2 = (uint32_t)(pa >> 32) ^ (c3 ^ (k1 + 2u * 0xBB67AE85u));
       c0 = n0; c1 = (uint32_t)pb; c2 = n2; c3 = (uint32_t)pa;
-      q0 += 0x9E3779B9u;
-      q1 += 0xBB67AE85u;
     }
 #pragma unroll
-    for (int r = 3; r < 10; ++r) {
+    for (int r = 1; r < 8; ++r) {
       const uint64_t pa = (uint64_t)0xD2511F53u * c0;
       const uint64_t pb = (uint64_t)0xCD9E8D57u * c2;
-      const uint32_t n0 = xor3_s((uint32_t)(pb >> 32), c1, q0);
-      const uint32_t n2 = xor3_s((uint32_t)(pa >> 32), c3, q1);
+      const uint32_t n0 = xor3_v((uint32_t)(pb >> 32), c1, r0[r]);
+      const uint32_t n2 = xor3_v((uint32_t)(pa >> 32), c3, r1[r]);
       c0 = n0; c1 = (uint32_t)pb; c2 = n2; c3 = (uint32_t)pa;
-      q0 += 0x9E3779B9u;
-      q1 += 0xBB67AE85u;
     }
     Words4 o;
     o.w[0] = c0; o.w[1] = c1; o.w[2] = c2; o.w[3] = c3;
@@ -236,21 +251,13 @@ struct MetPhilox {
 // seven base addresses are formed (own row, x row shifted by p, the one
 // wrapped x neighbour shared by the last and first site, and the four y/z
 // rows); every site reads its words at compile-time offsets from them.
-//
-// Metropolis test (+-J): nu = number of unsatisfied bonds at the site (own
-// bit ^ neighbour bit ^ [J = -1]); flipping changes the energy by
-// dE = 12 - 4 nu, and the move is accepted iff its draw is below thr_of_nu[nu]
-// (floor(2^32 exp(-beta dE)) for nu <= 2, 2^32 for nu >= 3).  The colour
-// passes below sum the post-move energy in the colour-1 pass of the last
-// sweep (every bond joins one site of each colour).
 struct TileCtx {
   uint32_t* lds;
-  const unsigned long long* thr_of_nu;
+  const unsigned long long* thr_of_nu;  // LDS address 0
   uint32_t hoff;   // byte offset of this lane's half word: 4 * (lane >> 5)
   uint32_t pos;    // this lane's bit in its half word
   MetPhilox ph;
   uint32_t t;
-  bool any_draw;
   unsigned long long writers;  // lanes 0 and 32: the lanes that apply a site's flips
   uint32_t hshift;             // 8 hoff: shift of a ballot that brings this lane's half down
   // kModelGauss16
@@ -375,24 +382,6 @@ __device__ __forceinline__ uint32_t real_pattern(const TileCtx& c, const SiteLoa
   return y;
 }
 
-// ---------------------------------------------------------------------------
-// +-J colour pass in two phases.  The bond arithmetic of a site is the same
-// for its 64 replicas up to their bits, so it is done once per site on whole
-// 32-bit words: phase 1 gives each lane one site (lane = site), forms the six
-// words x_k = neighbour ^ own ^ J mask (bit r set iff bond k of replica r is
-// unsatisfied), adds them bitwise with two full adders and a half adder into
-// three bit planes, nu = p0 + 2 p1 + 4 p2 per replica, and spreads the planes
-// into one byte per replica holding 8 nu, the byte address of the replica's
-// threshold.  Phase 2 returns to lane = replica: each lane reads its byte and
-// applies the Metropolis test with the same draw as before.  nu, the draws and
-// the test are unchanged, so every result is too.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t xor3_v(uint32_t a, uint32_t b, uint32_t c) {
-  uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0x96" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
-
 // bitwise majority of three words (v_bitop3_b32 truth table 0xe8)
 __device__ __forceinline__ uint32_t maj3_v(uint32_t a, uint32_t b, uint32_t c) {
   uint32_t r;
@@ -407,11 +396,7 @@ struct NuPlanes {
 // nu of 32 replicas as bit planes: x0 + .. + x5 = (s1 + 2 c1) + (s2 + 2 c2)
 // = p0 + 2 (c1 + c2 + c3) with p0 = s1 ^ s2, c3 = s1 & s2, and c1 + c2 + c3 =
 // p1 + 2 p2 (their XOR and majority).
-__device__ __forceinline__ NuPlanes nu_planes(uint32_t own, const uint32_t (&nb)[6],
-                                              const uint32_t (&jm)[6]) {
-  uint32_t x[6];
-#pragma unroll
-  for (int k = 0; k < 6; ++k) x[k] = xor3_v(nb[k], own, jm[k]);
+__device__ __forceinline__ NuPlanes nu_sum(const uint32_t (&x)[6]) {
   const uint32_t s1 = xor3_v(x[0], x[1], x[2]), c1 = maj3_v(x[0], x[1], x[2]);
   const uint32_t s2 = xor3_v(x[3], x[4], x[5]), c2 = maj3_v(x[3], x[4], x[5]);
   const uint32_t c3 = s1 & s2;
@@ -422,45 +407,16 @@ __device__ __forceinline__ NuPlanes nu_planes(uint32_t own, const uint32_t (&nb)
   return r;
 }
 
-// Word j (j = 0..7) of a half's 32 bytes: byte m holds 8 nu of the replica at
-// bit j + 8m of the planes.  With p1 rotated left by 1 and p2 by 2 (once per
-// half), the bits that word j needs sit at positions j, j + 1, j + 2 (mod 8)
-// of p0, p1', p2' and never overlap: three masked merges collect them and one
-// rotation right by j - 3 moves bit j + 8m of p0 to 8m + 3, of p1 to 8m + 4
-// and of p2 to 8m + 5.  The replica at bit b of a half therefore finds its
-// byte at 4 (b & 7) + (b >> 3) (plane_byte below).
+__device__ __forceinline__ NuPlanes nu_planes(uint32_t own, const uint32_t (&nb)[6],
+                                              const uint32_t (&jm)[6]) {
+  uint32_t x[6];
+#pragma unroll
+  for (int k = 0; k < 6; ++k) x[k] = xor3_v(nb[k], own, jm[k]);
+  return nu_sum(x);
+}
+
 __device__ __forceinline__ uint32_t rotr32(uint32_t x, uint32_t s) {
   return __builtin_amdgcn_alignbit(x, x, s);
-}
-
-struct NuPlanesRot {
-  uint32_t p0, p1r, p2r;  // p0, p1 rotated left by 1, p2 rotated left by 2
-};
-
-__device__ __forceinline__ NuPlanesRot rot_planes(const NuPlanes& p) {
-  NuPlanesRot r;
-  r.p0 = p.p0;
-  r.p1r = rotr32(p.p1, 31);
-  r.p2r = rotr32(p.p2, 30);
-  return r;
-}
-
-template <int J>
-__device__ __forceinline__ uint32_t nu8_word(const NuPlanesRot& p) {
-  constexpr uint32_t m = 0x01010101u << J;
-  constexpr uint32_t m1 = (m << 1) | (m >> 31), m2 = (m << 2) | (m >> 30);
-  const uint32_t t = (p.p0 & m) | (p.p1r & m1) | (p.p2r & m2);
-  return rotr32(t, (J - 3) & 31);
-}
-
-// The two-plane form of the same spread for the class c = min(nu, 3) of a
-// replica (c0 = p0 | p2, c1 = p1 | p2, c1 rotated left by 1 once per half):
-// word J, byte m holds 8 c of the replica at bit J + 8m, at bits 3 and 4.
-template <int J>
-__device__ __forceinline__ uint32_t cls8_word(uint32_t c0, uint32_t c1r) {
-  constexpr uint32_t m = 0x01010101u << J;
-  constexpr uint32_t m1 = (m << 1) | (m >> 31);
-  return rotr32((c0 & m) | (c1r & m1), (J - 3) & 31);
 }
 
 // byte of replica r (lane r) within a site's 64 bytes, before the rotation below
@@ -468,7 +424,7 @@ __device__ __forceinline__ uint32_t plane_byte(uint32_t r) {
   return (r & 32u) + 4u * (r & 7u) + ((r >> 3) & 3u);
 }
 
-// The +-J colour pass gives each wave one contiguous range of the colour's
+// The Gaussian colour pass gives each wave one contiguous range of the colour's
 // sites (same-colour sites are independent, and a range that starts on a
 // multiple of 4 holds whole Philox groups), taken 64 sites (one per lane in
 // phase 1) at a time.  W sites per wave: an even share rounded up to whole
@@ -485,74 +441,6 @@ constexpr uint32_t wave_sites() {
 // 16 (or 8) lanes the LDS serves together in different banks, for 64 banks
 // of 4 bytes and for 32; unrotated, lanes 64 bytes apart share banks.
 __host__ __device__ constexpr uint32_t plane_rot(uint32_t e) { return ((e >> 1) + (e >> 3)) & 3u; }
-
-// Phase 1 for a chunk of n <= 64 sites from colour-major index cm0: lane e < n
-// takes site cm0 + e, reads its six neighbours' words (absolute LDS addresses
-// from the site table) and its own, forms the bit planes of nu for both
-// 32-replica halves and writes its plane entry.
-//
-// FAST (every move that raises the energy has a threshold below 2^32): the
-// replicas with nu >= 3, whose move does not raise the energy and is always
-// taken, are flipped here, in the site's word, and the bytes hold 8 min(nu, 3).
-// Phase 2 then reads the low 32-bit word of the threshold table at that byte:
-// thr(nu) for nu <= 2, and 0 (never, the move is done) for nu >= 3.  Only this
-// wave writes the words of its own sites during the pass, and phase 2 does not
-// read them, so the early flip changes nothing but the order of the XORs.
-// Otherwise the bytes hold 8 nu (the 64-bit table's byte address).
-template <bool FAST>
-__device__ __forceinline__ void plane_chunk(const TileCtx& c, const PlaneSite* __restrict__ sites,
-                                            uint32_t cm0, uint32_t n, uint32_t lane,
-                                            char* planes) {
-  if (lane < n) {
-    const uint32_t cm = cm0 + lane;
-    const uint4 e0 = reinterpret_cast<const uint4*>(sites)[2 * cm];
-    const uint4 e1 = reinterpret_cast<const uint4*>(sites)[2 * cm + 1];
-    const uint32_t nb8[6] = {e0.x, e0.y, e0.z, e0.w, e1.x, e1.y};
-    const uint32_t jneg = e1.z;
-    uint2* w = reinterpret_cast<uint2*>(c.lds);
-    // LDS address 0: the table's addresses are absolute (the kernel has
-    // checked that the tile image starts at kTileLdsBase)
-    const char* lds0 = reinterpret_cast<const char*>(c.thr_of_nu);
-    const uint2 o = w[cm];
-    uint32_t lo[6], hi[6], jm[6];
-#pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const uint2 v = *reinterpret_cast<const uint2*>(lds0 + nb8[k]);
-      lo[k] = v.x;
-      hi[k] = v.y;
-      jm[k] = (uint32_t)((int32_t)(jneg << (31 - k)) >> 31);
-    }
-    const NuPlanes pa = nu_planes(o.x, lo, jm);
-    const NuPlanes pb = nu_planes(o.y, hi, jm);
-    uint4 q[4];
-    if constexpr (FAST) {
-      // nu >= 3: p2 | (p1 & p0); flipped now
-      w[cm] = make_uint2(o.x ^ (pa.p2 | (pa.p1 & pa.p0)), o.y ^ (pb.p2 | (pb.p1 & pb.p0)));
-      const uint32_t a0 = pa.p0 | pa.p2, a1 = rotr32(pa.p1 | pa.p2, 31);
-      const uint32_t b0 = pb.p0 | pb.p2, b1 = rotr32(pb.p1 | pb.p2, 31);
-      q[0] = make_uint4(cls8_word<0>(a0, a1), cls8_word<1>(a0, a1), cls8_word<2>(a0, a1),
-                        cls8_word<3>(a0, a1));
-      q[1] = make_uint4(cls8_word<4>(a0, a1), cls8_word<5>(a0, a1), cls8_word<6>(a0, a1),
-                        cls8_word<7>(a0, a1));
-      q[2] = make_uint4(cls8_word<0>(b0, b1), cls8_word<1>(b0, b1), cls8_word<2>(b0, b1),
-                        cls8_word<3>(b0, b1));
-      q[3] = make_uint4(cls8_word<4>(b0, b1), cls8_word<5>(b0, b1), cls8_word<6>(b0, b1),
-                        cls8_word<7>(b0, b1));
-    } else {
-      const NuPlanesRot a = rot_planes(pa);
-      const NuPlanesRot b = rot_planes(pb);
-      q[0] = make_uint4(nu8_word<0>(a), nu8_word<1>(a), nu8_word<2>(a), nu8_word<3>(a));
-      q[1] = make_uint4(nu8_word<4>(a), nu8_word<5>(a), nu8_word<6>(a), nu8_word<7>(a));
-      q[2] = make_uint4(nu8_word<0>(b), nu8_word<1>(b), nu8_word<2>(b), nu8_word<3>(b));
-      q[3] = make_uint4(nu8_word<4>(b), nu8_word<5>(b), nu8_word<6>(b), nu8_word<7>(b));
-    }
-    char* const entry = planes + 64 * lane;
-    const uint32_t rot = plane_rot(lane);
-#pragma unroll
-    for (uint32_t j = 0; j < 4; ++j)
-      *reinterpret_cast<uint4*>(entry + 16 * ((j + rot) & 3u)) = q[j];
-  }
-}
 
 // XOR of data into the LDS word at addr + OFF by the two lanes in `writers`
 // (lanes 0 and 32: one per 32-replica half of a site word), under an exec
@@ -589,82 +477,109 @@ __device__ __forceinline__ uint32_t plane_read(const PlaneReads& pr) {
   return (uint32_t)pr.at[plane_rot(E)][64 * E];
 }
 
-// Phase 2 for sites E.. of a chunk of n sites (n uniform): the Metropolis
-// test of this lane's replica at each site, and the flip.  A new Philox call
-// starts every fourth site, whether or not a draw can matter (a threshold of
-// 0 or 2^32 decides without it), so that each group of four sites is one
-// basic block; the chunk ends at the first group at or past n.  The byte of
-// site E + 1 of the same group is read before site E is updated (the plane
-// area is not written in this phase), so its LDS latency overlaps the update.
-//
-// FAST: the byte is 8 min(nu, 3) and the threshold the table's low 32-bit
-// word (see plane_chunk): one 32-bit compare.  Otherwise the byte is 8 nu and
-// the threshold the whole 64-bit entry (2^32: always taken); with ACCUM the
-// lane also sums its replica's post-move nu.
-template <int E, bool FAST, bool ACCUM>
-__device__ __forceinline__ void chunk_sites(const TileCtx& c, const char* ownb,
-                                            const PlaneReads& pr, uint32_t g0, uint32_t n,
-                                            Words4& d, uint32_t& usum, uint32_t a8) {
-  if constexpr (E % 4 == 0) {
-    if ((uint32_t)E >= n) return;
-    a8 = plane_read<E>(pr);
-    d = c.ph.draw(c.t, g0 + (uint32_t)(E / 4));
-  }
-  uint32_t nx = 0;
-  if constexpr (E % 4 != 3) nx = plane_read<E + 1>(pr);
-  bool acc;
-  if constexpr (FAST) {
-    const uint32_t thr =
-        *reinterpret_cast<const uint32_t*>(reinterpret_cast<const char*>(c.thr_of_nu) + a8);
-    acc = d.w[E % 4] < thr;
-  } else {
-    const unsigned long long thr = *reinterpret_cast<const unsigned long long*>(
-        reinterpret_cast<const char*>(c.thr_of_nu) + a8);
-    acc = (unsigned long long)d.w[E % 4] < thr;
-    if (ACCUM) {
-      const uint32_t nu = a8 >> 3;
-      usum += acc ? 6u - nu : nu;
-    }
-  }
-  // this lane's half of the ballot: one 64-bit shift of the scalar mask
-  const uint32_t fh = (uint32_t)(__ballot(acc) >> c.hshift);
-  lds_xor_two_lanes<8 * E>(ownb, fh, c.writers);
-  if constexpr (E + 1 < 64) chunk_sites<E + 1, FAST, ACCUM>(c, ownb, pr, g0, n, d, usum, nx);
+// ---------------------------------------------------------------------------
+// Counting over sites for 64 replicas (or pairs of replicas) at a time.  With
+// lane = site, a lane's words hold one bit per replica; the number of set bits
+// per replica is kept as bit planes (plane k: bit k of the 64 counts), added
+// with full adders on whole words, first within a lane, then across the lanes
+// of the wave.
+// ---------------------------------------------------------------------------
+typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(1))) U32x2 GlobalU32x2;
+typedef const __attribute__((address_space(1))) U32x4 GlobalU32x4;
+
+struct FullSum {
+  uint32_t s, c;
+};
+__device__ __forceinline__ FullSum full_add(uint32_t a, uint32_t b, uint32_t c) {
+  FullSum r;
+  r.s = xor3_v(a, b, c);
+  r.c = maj3_v(a, b, c);
+  return r;
 }
 
-// One +-J colour pass of this wave over its range of wave_sites() sites, a
-// 64-site chunk at a time: phase 1 for the chunk, then phase 2.  The wave's
-// plane area holds one chunk.  FAST passes skip phase 2 when no move that
-// raises the energy can be taken (every such threshold 0): phase 1 has done
-// all the flips.  The pass ends with a workgroup barrier, so the next colour
-// sees every flip.
-template <int L, int SPLIT, bool FAST, bool ACCUM>
-__device__ uint32_t sweep_colour_planes(const TileCtx& c, const PlaneSite* __restrict__ sites,
-                                        uint32_t colour, uint32_t part, char* planes,
-                                        const PlaneReads& pr, uint32_t lane) {
-  static_assert(!(FAST && ACCUM), "the energy is summed by the 64-bit form of the pass");
-  constexpr uint32_t N = L * L * L, HALF = N / 2, W = wave_sites<L, SPLIT>();
-  const uint32_t own0 = colour * HALF;
-  const uint32_t first = part * W;
-  const uint32_t last = min(first + W, HALF);
-  uint32_t usum = 0;
-  Words4 d;
-  d.w[0] = d.w[1] = d.w[2] = d.w[3] = 0u;
-  const char* const own_h = reinterpret_cast<const char*>(c.lds) + c.hoff;
-  const bool phase2 = !FAST || c.any_draw;
-  for (uint32_t s0 = first; s0 < last; s0 += 64) {
-    const uint32_t n = __builtin_amdgcn_readfirstlane(min(64u, last - s0));
-    const uint32_t cm0 = own0 + s0;
-    plane_chunk<FAST>(c, sites, cm0, n, lane, planes);
-    __builtin_amdgcn_wave_barrier();
-    if (phase2) {
-      const char* ownb = own_h + whole_s(8 * cm0);
-      chunk_sites<0, FAST, ACCUM>(c, ownb, pr, cm0 >> 2, n, d, usum, 0u);
-    }
-    __builtin_amdgcn_wave_barrier();
+// p += q (NP planes each), the sum in NP + 1 planes of p.
+template <int NP>
+__device__ __forceinline__ void planes_add(uint32_t* p, const uint32_t* q) {
+  uint32_t c = p[0] & q[0];
+  p[0] ^= q[0];
+#pragma unroll
+  for (int k = 1; k < NP; ++k) {
+    const FullSum f = full_add(p[k], q[k], c);
+    p[k] = f.s;
+    c = f.c;
   }
-  __syncthreads();
-  return usum;
+  p[NP] = c;
+}
+
+// p += the same planes of the lane a DPP control pairs this one with.
+template <int NP, int CTRL>
+__device__ __forceinline__ void planes_add_dpp(uint32_t* p) {
+  uint32_t q[NP];
+#pragma unroll
+  for (int k = 0; k < NP; ++k)
+    q[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)p[k], CTRL, 0xF, 0xF, true);
+  planes_add<NP>(p, q);
+}
+
+// The count of this lane's pair: lo and hi are every lane's NP-plane counts of
+// pairs 0..31 and 32..63.  One swap of the wave's halves leaves lanes 0..31
+// with the sums of the first 32 pairs and lanes 32..63 with those of the
+// others (half the planes to carry on); five more additions cover the 32 lanes
+// of a half: across the two rows of 16, then i with 15 - i, 7 - i, i ^ 2 and
+// i ^ 1 within a row, which together reach all 16.
+template <int NP>
+__device__ __forceinline__ uint32_t lane_count(const uint32_t (&lo)[NP], const uint32_t (&hi)[NP]) {
+  uint32_t p[NP + 6], q[NP + 1];
+#pragma unroll
+  for (int k = 0; k < NP; ++k) {
+    const auto r = __builtin_amdgcn_permlane32_swap(lo[k], hi[k], false, false);
+    p[k] = r[0];
+    q[k] = r[1];
+  }
+  planes_add<NP>(p, q);
+#pragma unroll
+  for (int k = 0; k < NP + 1; ++k) {
+    const auto r = __builtin_amdgcn_permlane16_swap(p[k], p[k], false, false);
+    p[k] = r[0];
+    q[k] = r[1];
+  }
+  planes_add<NP + 1>(p, q);
+  planes_add_dpp<NP + 2, 0x140>(p);  // row_mirror
+  planes_add_dpp<NP + 3, 0x141>(p);  // row_half_mirror
+  planes_add_dpp<NP + 4, 0x4E>(p);   // quad_perm 2,3,0,1
+  planes_add_dpp<NP + 5, 0xB1>(p);   // quad_perm 1,0,3,2
+  const uint32_t pos = lane_id() & 31u;
+  uint32_t d = 0;
+#pragma unroll
+  for (int k = 0; k < NP + 6; ++k) d |= bit_of(p[k], pos) << k;
+  return d;
+}
+
+// p += nu of the same replicas, given as three planes.
+template <int NP>
+__device__ __forceinline__ void planes_add_nu(uint32_t (&p)[NP], const NuPlanes& q) {
+  const uint32_t x[3] = {q.p0, q.p1, q.p2};
+  uint32_t c = p[0] & x[0];
+  p[0] ^= x[0];
+#pragma unroll
+  for (int k = 1; k < 3; ++k) {
+    const FullSum f = full_add(p[k], x[k], c);
+    p[k] = f.s;
+    c = f.c;
+  }
+#pragma unroll
+  for (int k = 3; k < NP; ++k) {
+    const uint32_t n = p[k] & c;
+    p[k] ^= c;
+    c = n;
+  }
+}
+
+// Bit 1 of the four bytes of x (0 or 1 each) as bits 0..3.
+__device__ __forceinline__ uint32_t bytes_to_bits(uint32_t x) {
+  return (((x >> 1) & 0x01010101u) * 0x10204080u) >> 28;
 }
 
 // ---------------------------------------------------------------------------
@@ -699,7 +614,7 @@ constexpr int pattern_shift() {
 // bit that word J needs from plane k sits at J + k + 8m (mod 32): the six
 // masked merges never overlap (k < 8), and one rotation right by J - B moves
 // it to 8m + B + k.  The replica at bit b of a half finds its byte where the
-// +-J pass puts it (plane_byte).
+// plane_byte says.
 template <int J, int B>
 __device__ __forceinline__ uint32_t pattern_word(const uint32_t (&xr)[6]) {
   constexpr uint32_t m = 0x01010101u << J;
@@ -710,7 +625,7 @@ __device__ __forceinline__ uint32_t pattern_word(const uint32_t (&xr)[6]) {
 }
 
 // Phase 1 of the Gaussian pass for a chunk of n <= 64 sites from colour-major
-// index cm0 (see plane_chunk: same site table, same entry layout).  Lanes past
+// index cm0: lane e takes site cm0 + e and writes its plane entry.  Lanes past
 // n take site n - 1 again, so that every entry of the area holds a pattern of
 // a site of the chunk (phase 2 reads one group past the chunk's end ahead).
 template <int M>
@@ -922,7 +837,7 @@ __device__ __forceinline__ void pattern_groups(const TileCtx& c, const char* own
 }
 
 // One Gaussian colour pass of this wave over its range of wave_sites() sites,
-// a 64-site chunk at a time (see sweep_colour_planes).
+// a 64-site chunk at a time (see wave_sites).
 template <int L, int SPLIT, int M, bool ACCUM>
 __device__ typename AccOf<M>::type sweep_colour_patterns(const TileCtx& c,
                                                          const PlaneSite* __restrict__ sites,
@@ -1635,14 +1550,12 @@ __global__ __launch_bounds__(kBlockCounts) void k_scan_scatter(BatchDev B, Group
 // of each tile by the same factor.
 //
 // Register budget: as many waves per SIMD as fit without spilling to scratch
-// memory (+-J: eight up to L = 10, seven at L = 12, six above; quantised
-// Gaussian couplings, whose update holds six coupling values: seven up to
-// L = 8, six at 10, five at 12 and 14, four at 16).
+// memory (seven up to L = 8, six at 10, five at 12 and 14, four at 16).  (+-J
+// populations: k_sweep_pm.)
 template <int L, int M>
 constexpr int sweep_min_waves_per_eu() {
-  if constexpr (M == (int)kModelGauss16) return L <= 8 ? 7 : L == 10 ? 6 : L <= 14 ? 5 : 4;
-  if constexpr (M == (int)kModelReal) return L <= 8 ? 7 : L == 10 ? 6 : L <= 14 ? 5 : 4;
-  return L <= 10 ? 8 : L == 12 ? 7 : 6;
+  static_assert(M == (int)kModelGauss16 || M == (int)kModelReal, "Gaussian models");
+  return L <= 8 ? 7 : L == 10 ? 6 : L <= 14 ? 5 : 4;
 }
 
 template <int LAYOUT, int L, int SPLIT, int M>
@@ -1650,7 +1563,8 @@ __global__ __launch_bounds__(64 * SPLIT)
 __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_sweep(BatchDev B,
                                                                                 Group G) {
   constexpr uint32_t N = L * L * L;
-  __shared__ unsigned long long thr_of_nu[8];  // first LDS object: address 0 (see chunk_sites)
+  __shared__ unsigned long long thr_of_nu[8];  // first LDS object: its address, 0, is the base of
+                                               // the absolute LDS addresses below
   extern __shared__ uint32_t lds_all[];
   const Member m = member_of(G);
   const DevPop P = B.pops[m.pop];
@@ -1672,12 +1586,11 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_swee
       __builtin_amdgcn_readfirstlane(m.lb < active ? xcd_block(m.lb, active) : m.lb);
   // whole workgroups leave together (the passes below use workgroup barriers)
   if (tile * 64 >= Rs) return;
-  // Phase 2 of the +-J pass indexes the threshold table by byte address 8 nu:
-  // it must sit at LDS address 0; phase 1 of the colour passes reads the tile
-  // image at the absolute addresses of its site table, so the image must start
-  // at kTileLdsBase; the Gaussian pass reads the dE16 table at the address
-  // that follows from both.  If the toolchain ever places them elsewhere, report a
-  // configuration error instead of computing with wrong addresses.
+  // Phase 1 of the colour passes reads the tile image at the absolute addresses
+  // of its site table, so the image must start at kTileLdsBase; phase 2 reads
+  // the dE16 table at the address that follows from it.  If the toolchain ever
+  // places them elsewhere, report a configuration error instead of computing
+  // with wrong addresses.
   if ((uint32_t)(uintptr_t)thr_of_nu != 0u || (uint32_t)(uintptr_t)lds_all != kTileLdsBase) {
     if (threadIdx.x == 0) {
       P.sc->err = 2u;
@@ -1685,11 +1598,7 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_swee
     }
     return;
   }
-  if (threadIdx.x < 8)
-    thr_of_nu[threadIdx.x] = threadIdx.x == 0   ? sp.thr[2]
-                             : threadIdx.x == 1 ? sp.thr[1]
-                             : threadIdx.x == 2 ? sp.thr[0]
-                                                : (1ull << 32);
+  if (threadIdx.x == 0) thr_of_nu[0] = 0;
   uint32_t* const lds = lds_all;
   // kModelGauss16: the dE16 threshold table, after the tile image and the
   // waves' plane areas (visible after the gather's barrier)
@@ -1708,16 +1617,8 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_swee
   c.hoff = 4u * (lane >> 5);
   c.pos = lane & 31u;
   c.ph.init(j, (uint32_t)P.seed, (uint32_t)(P.seed >> 32));
-  // A draw matters only for a class whose threshold is neither 0 nor 2^32.
-  // (kModelGauss16: the host passes the largest and the smallest threshold of
-  // a positive move, the table's dE16 = 2 and last entries, in thr[0] and
-  // thr[1], and 0 in thr[2]; the table is non-increasing, so a draw matters
-  // unless both are 0 or both are 2^32.)
   c.writers = 0x0000000100000001ull;
   c.hshift = 8u * c.hoff;
-  c.any_draw = (sp.thr[0] != 0 && sp.thr[0] < (1ull << 32)) ||
-               (sp.thr[1] != 0 && sp.thr[1] < (1ull << 32)) ||
-               (sp.thr[2] != 0 && sp.thr[2] < (1ull << 32));
   c.rowk = P.rowk;
   c.rowk_stride = P.rowk_stride;
   c.gaddr = P.gaddr;
@@ -1740,35 +1641,14 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_swee
         pr.at[k] = reinterpret_cast<const uint8_t*>(planes) + 16u * (((pb >> 4) + k) & 3u) +
                    (pb & 15u);
     }
-    if constexpr (M != (int)kModelPm) {
-      for (uint32_t s = 0; s + 1 < sp.n_sweeps; ++s) {
-        c.t = sp.t0 + s;
-        sweep_colour_patterns<L, SPLIT, M, false>(c, P.psites, 0u, part, planes, pr, lane);
-        sweep_colour_patterns<L, SPLIT, M, false>(c, P.psites, 1u, part, planes, pr, lane);
-      }
-      c.t = sp.t0 + sp.n_sweeps - 1;
+    for (uint32_t s = 0; s + 1 < sp.n_sweeps; ++s) {
+      c.t = sp.t0 + s;
       sweep_colour_patterns<L, SPLIT, M, false>(c, P.psites, 0u, part, planes, pr, lane);
-      U = sweep_colour_patterns<L, SPLIT, M, true>(c, P.psites, 1u, part, planes, pr, lane);
-    } else {
-      // every move that raises the energy has a threshold below 2^32 (beta
-      // not 0 in double precision): the passes take the 32-bit form, but for
-      // the last colour-1 pass, which also sums the energy
-      const bool fast = sp.thr[0] < (1ull << 32);
-      for (uint32_t s = 0; s < sp.n_sweeps; ++s) {
-        c.t = sp.t0 + s;
-        for (uint32_t colour = 0; colour < 2; ++colour) {
-          if (s + 1 == sp.n_sweeps && colour == 1)
-            U = sweep_colour_planes<L, SPLIT, false, true>(c, P.psites, 1u, part, planes, pr,
-                                                           lane);
-          else if (fast)
-            sweep_colour_planes<L, SPLIT, true, false>(c, P.psites, colour, part, planes, pr,
-                                                       lane);
-          else
-            sweep_colour_planes<L, SPLIT, false, false>(c, P.psites, colour, part, planes, pr,
-                                                        lane);
-        }
-      }
+      sweep_colour_patterns<L, SPLIT, M, false>(c, P.psites, 1u, part, planes, pr, lane);
     }
+    c.t = sp.t0 + sp.n_sweeps - 1;
+    sweep_colour_patterns<L, SPLIT, M, false>(c, P.psites, 0u, part, planes, pr, lane);
+    U = sweep_colour_patterns<L, SPLIT, M, true>(c, P.psites, 1u, part, planes, pr, lane);
   }
   // Epilogue.  The lane number, the slot, its source and the descriptor
   // fields are formed or read again here rather than held in registers
@@ -1801,6 +1681,9 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_swee
     pick(P2.fam, nxt2)[j2] = pick(P2.fam, cur2)[src2];
   }
 }
+
+// the +-J sweep kernel
+#include "pa_sweep_pm.inc"
 
 // The energy word recomputed from the stored spins of buffer cur (after an
 // import; for kModelGauss16 also after the initial spins are drawn), or, with
@@ -1914,85 +1797,6 @@ __global__ __launch_bounds__(256) void k_record(BatchDev B, Group G) {
     rec->R_new = P.sc->R_tilde;
     rec->sum_eta2 = P.sc->sum_eta2;
   }
-}
-
-// ---------------------------------------------------------------------------
-// Counting over sites for 64 pairs at a time.  With lane = site, a lane's words
-// hold one bit per pair; the number of set bits per pair is kept as bit planes
-// (plane k: bit k of the 64 pairs' counts), added with full adders on whole
-// words, first within a lane, then across the lanes of the wave.
-// ---------------------------------------------------------------------------
-typedef uint32_t U32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t U32x4 __attribute__((ext_vector_type(4)));
-typedef const __attribute__((address_space(1))) U32x2 GlobalU32x2;
-typedef const __attribute__((address_space(1))) U32x4 GlobalU32x4;
-
-struct FullSum {
-  uint32_t s, c;
-};
-__device__ __forceinline__ FullSum full_add(uint32_t a, uint32_t b, uint32_t c) {
-  FullSum r;
-  r.s = xor3_v(a, b, c);
-  r.c = maj3_v(a, b, c);
-  return r;
-}
-
-// p += q (NP planes each), the sum in NP + 1 planes of p.
-template <int NP>
-__device__ __forceinline__ void planes_add(uint32_t* p, const uint32_t* q) {
-  uint32_t c = p[0] & q[0];
-  p[0] ^= q[0];
-#pragma unroll
-  for (int k = 1; k < NP; ++k) {
-    const FullSum f = full_add(p[k], q[k], c);
-    p[k] = f.s;
-    c = f.c;
-  }
-  p[NP] = c;
-}
-
-// p += the same planes of the lane a DPP control pairs this one with.
-template <int NP, int CTRL>
-__device__ __forceinline__ void planes_add_dpp(uint32_t* p) {
-  uint32_t q[NP];
-#pragma unroll
-  for (int k = 0; k < NP; ++k)
-    q[k] = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)p[k], CTRL, 0xF, 0xF, true);
-  planes_add<NP>(p, q);
-}
-
-// The count of this lane's pair: lo and hi are every lane's NP-plane counts of
-// pairs 0..31 and 32..63.  One swap of the wave's halves leaves lanes 0..31
-// with the sums of the first 32 pairs and lanes 32..63 with those of the
-// others (half the planes to carry on); five more additions cover the 32 lanes
-// of a half: across the two rows of 16, then i with 15 - i, 7 - i, i ^ 2 and
-// i ^ 1 within a row, which together reach all 16.
-template <int NP>
-__device__ __forceinline__ uint32_t lane_count(const uint32_t (&lo)[NP], const uint32_t (&hi)[NP]) {
-  uint32_t p[NP + 6], q[NP + 1];
-#pragma unroll
-  for (int k = 0; k < NP; ++k) {
-    const auto r = __builtin_amdgcn_permlane32_swap(lo[k], hi[k], false, false);
-    p[k] = r[0];
-    q[k] = r[1];
-  }
-  planes_add<NP>(p, q);
-#pragma unroll
-  for (int k = 0; k < NP + 1; ++k) {
-    const auto r = __builtin_amdgcn_permlane16_swap(p[k], p[k], false, false);
-    p[k] = r[0];
-    q[k] = r[1];
-  }
-  planes_add<NP + 1>(p, q);
-  planes_add_dpp<NP + 2, 0x140>(p);  // row_mirror
-  planes_add_dpp<NP + 3, 0x141>(p);  // row_half_mirror
-  planes_add_dpp<NP + 4, 0x4E>(p);   // quad_perm 2,3,0,1
-  planes_add_dpp<NP + 5, 0xB1>(p);   // quad_perm 1,0,3,2
-  const uint32_t pos = lane_id() & 31u;
-  uint32_t d = 0;
-#pragma unroll
-  for (int k = 0; k < NP + 6; ++k) d |= bit_of(p[k], pos) << k;
-  return d;
 }
 
 // One 32-pair half of the words of eight sites added to a 7-plane count (at
@@ -2145,11 +1949,6 @@ __global__ __launch_bounds__(64 * kOverlapTiles) void k_overlap_pair(DevPop A, D
   overlap_tiles<LAYOUT>(A, Bp, cur_a, cur_b, blockIdx.x, A.ovl_hist);
 }
 
-// Bit 1 of the four bytes of x (0 or 1 each) as bits 0..3.
-__device__ __forceinline__ uint32_t bytes_to_bits(uint32_t x) {
-  return (((x >> 1) & 0x01010101u) * 0x10204080u) >> 28;
-}
-
 // Link-overlap histogram (Sec. II.A): slot i of population a against slot i
 // of population b, one 64-pair tile per wave.  With x_n = s^a_n s^b_n a bond
 // <n,m> contributes x_n x_m, so only the bonds whose ends differ in x count:
@@ -2157,7 +1956,7 @@ __device__ __forceinline__ uint32_t bytes_to_bits(uint32_t x) {
 // words go to LDS (colour-major, 64 pairs per site, 8N bytes).  For even L
 // every bond joins a colour-0 site to a colour-1 site, so the six bonds of
 // every colour-0 site cover each bond once: lane = colour-0 site, the six
-// words own ^ neighbour added into planes (as the +-J colour pass does), the
+// words own ^ neighbour added into planes (nu_sum), the
 // sites of a lane and then the lanes added in planes (see lane_count).  At L = 10 about 900 instructions per 64 pairs, where a masked XOR
 // and a population count per bond and pair take 6000 (163 us at R = 5e5
 // before); what is left is bound by the loads.
@@ -2210,24 +2009,8 @@ __global__ __launch_bounds__(64) void k_link_overlap(DevPop A, DevPop Bp, uint32
       nh[k] = v.y;
     }
     const NuPlanes pl = nu_planes(o.x, nl, none), ph = nu_planes(o.y, nh, none);
-    const uint32_t ql[3] = {pl.p0, pl.p1, pl.p2}, qh[3] = {ph.p0, ph.p1, ph.p2};
-    uint32_t cl = 0, ch = 0;
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-      const FullSum fl = full_add(lo[k], ql[k], cl), fh = full_add(hi[k], qh[k], ch);
-      lo[k] = fl.s;
-      cl = fl.c;
-      hi[k] = fh.s;
-      ch = fh.c;
-    }
-#pragma unroll
-    for (int k = 3; k < NP; ++k) {
-      const uint32_t tl = lo[k] & cl, th = hi[k] & ch;
-      lo[k] ^= cl;
-      hi[k] ^= ch;
-      cl = tl;
-      ch = th;
-    }
+    planes_add_nu<NP>(lo, pl);
+    planes_add_nu<NP>(hi, ph);
   }
   const uint32_t d = lane_count<NP>(lo, hi);
   // each tile counts into copy tile mod kLinkCopies of the histogram, so that
@@ -2342,12 +2125,16 @@ void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t 
       hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelGauss16>), dim3(g.blocks), dim3(64 * 4), lds,
                          stream, B, g);
   } else {
+    const size_t lds_pm = kPmImage + (size_t)L * L * L * 8 * pm_tiles(L, split) +
+                          kPmPlaneBytes * pm_waves(split);
+    const dim3 grid(g.blocks), block(64 * pm_waves(split));
     if (split == 8)
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelPm>), dim3(g.blocks), dim3(64 * 8), lds,
+      hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, 8>), grid, block, lds_pm, stream, B, g);
+    else if (split == kPmPacked && L <= 8)
+      hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, L <= 8 ? kPmPacked : 4>), grid, block, lds_pm,
                          stream, B, g);
     else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelPm>), dim3(g.blocks), dim3(64 * 4), lds,
-                         stream, B, g);
+      hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, 4>), grid, block, lds_pm, stream, B, g);
   }
 }
 
@@ -2522,7 +2309,8 @@ hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream)
 hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint32_t L,
                         uint32_t split, uint32_t model, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
-  if (split != 4 && split != 8) return hipErrorInvalidValue;
+  if (split != 4 && split != 8 && !(split == kPmPacked && model == kModelPm && L <= 8))
+    return hipErrorInvalidValue;
   if (layout == 2) {
     PA_L_SWITCH_S(launch_sweep_l, 2)
   } else {

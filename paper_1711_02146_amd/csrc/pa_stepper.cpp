@@ -199,8 +199,9 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
     for (uint32_t p : kv.second) tiles += (pops[p]->dev.R + 63) / 64;
     const uint32_t split =
         pa::sweep_split_for(pa::kModelPm, kv.first.first, kv.first.second, tiles);
+    const uint32_t per_block = pa::sweep_tiles(pa::kModelPm, kv.first.second, split);
     std::vector<uint32_t> nb;
-    for (uint32_t p : kv.second) nb.push_back(pa::blocks_sweep(pops[p]->dev.capacity));
+    for (uint32_t p : kv.second) nb.push_back(pa::blocks_sweep(pops[p]->dev.capacity, per_block));
     g_sweep.push_back({kv.first.first, kv.first.second, split, gt.add(kv.second, nb)});
   }
   if (gt.u32.size() > l.n_u32) return PA_EINVAL;

@@ -38,9 +38,9 @@ uint32_t sweep_split_for(uint32_t model, uint32_t layout, uint32_t L, uint64_t t
   {
     std::lock_guard<std::mutex> lk(g_mu);
     const auto it = g_table.find({model, layout, L, size_class(tiles)});
-    if (it != g_table.end()) return it->second;
+    if (it != g_table.end()) return sweep_form(model, L, it->second, tiles);
   }
-  return sweep_split_default(model, L, tiles);
+  return sweep_form(model, L, sweep_split_default(model, L, tiles), tiles);
 }
 
 void sweep_split_record(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles,

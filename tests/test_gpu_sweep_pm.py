@@ -1,0 +1,81 @@
+"""The +-J sweep kernel against the oracle where its forms and branches change:
+workgroups with several tiles (L <= 8) with a part-filled last workgroup and a
+part-filled last tile, one tile on four and on eight waves with full, part and
+single-group chunks, the pass at inverse temperatures where an energy-raising
+move has a threshold of 2^32, a threshold of 0 for every move, and a copy step
+whose sources lie in one, several and many old tiles.  Spins, energy words and
+family labels must be equal, bit for bit."""
+import numpy as np
+import pytest
+
+import oracle
+import pa_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def pam():
+    import paper_1711_02146_amd as m
+
+    yield m
+    m.pa_autotune_reset()
+
+
+def pair(pam, L, R, seed, layout):
+    J = pa_inputs.couplings_pm(L, 31 + L)
+    return pam.Population(L, R, J, seed, layout=layout), oracle.Population(L, J, R, seed)
+
+
+def assert_state(g, o):
+    s, u, f = g.export_state()
+    assert s.shape[0] == o.R_tilde
+    np.testing.assert_array_equal(s.reshape(-1), o.spins)
+    np.testing.assert_array_equal(u.astype(np.int32), o.U)
+    np.testing.assert_array_equal(f, o.fam)
+
+
+# sizes on either side of the packed form's workgroups: 4 tiles at L = 4 and 6
+# (from 1500 tiles), 2 at L = 8 (from 3200)
+@pytest.mark.parametrize("layout", ["int8", "bitpack64"])
+@pytest.mark.parametrize("L,R", [(4, 1), (4, 64 * 5 + 1), (4, 64 * 600 + 3), (6, 64 * 1499),
+                                 (6, 64 * 1501 + 33), (8, 64 * 3199 + 1), (8, 64 * 3201 + 1)])
+def test_packed_forms(pam, layout, L, R):
+    pam.pa_autotune_reset()
+    g, o = pair(pam, L, R, 77 + R, layout)
+    for b in (0.3, 0.6):
+        g.resample(b)
+        o.resample(b)
+        g.sweep(b, 1)
+        o.sweep(b, 1)
+    assert_state(g, o)
+    g.close()
+
+
+@pytest.mark.parametrize("split", [4, 8])
+@pytest.mark.parametrize("L", [4, 6, 8, 10, 12, 14, 16])
+@pytest.mark.parametrize("beta", [0.0, 1e-17, 3e-17, 0.7, 20.0])
+def test_forms_and_thresholds(pam, L, split, beta):
+    R = 70
+    pam.pa_autotune_set(L, R, split)
+    g, o = pair(pam, L, R, 5 * L, "bitpack64")
+    g.sweep(beta, 2)
+    o.sweep(beta, 2)
+    assert_state(g, o)
+    pam.pa_autotune_reset()
+    g.close()
+
+
+@pytest.mark.parametrize("layout", ["int8", "bitpack64"])
+@pytest.mark.parametrize("L,dbeta", [(4, 0.05), (4, 1.0), (6, 0.4), (8, 0.25), (10, 0.3), (10, 1.5)])
+def test_copy_step_spread(pam, layout, L, dbeta):
+    """dbeta from a few per cent culled to a handful of survivors: the 64
+    sources of a new tile lie in two, several or very many old tiles."""
+    R = 5000
+    g, o = pair(pam, L, R, 9 * L + 1, layout)
+    g.resample(dbeta)
+    o.resample(dbeta)
+    g.sweep(dbeta, 1)
+    o.sweep(dbeta, 1)
+    assert_state(g, o)
+    g.close()
