@@ -133,10 +133,12 @@ bool make_layout(const pa_params* p, Layout* out) {
   l.off_rhe = take(real ? rows * pa::kRealPatterns * 8 : 0);
   l.off_rthr = take(real ? rows * pa::kRealPatterns * 8 : 0);
   l.off_rthr32 = take(real ? rows * pa::kRealPatterns * 4 : 0);
-  // (one per slot block for the copy counts, three per reduction workgroup
-  // for the bisection's evaluations)
-  const size_t n_part = std::max<size_t>(l.n_blocks, 3 * (size_t)pa::kRealSumBlocks);
+  // (one per slot block for the copy counts, kCullLanes per reduction workgroup
+  // for the constant-culling search)
+  const size_t n_part =
+      std::max<size_t>(l.n_blocks, (size_t)pa::kCullLanes * (size_t)pa::kRealSumBlocks);
   l.off_rpart = take(real ? n_part * sizeof(pa::RealPartial) : 0);
+  l.off_rsearch = take(real ? sizeof(pa::RealSearch) : 0);
   // PA_MODEL_GAUSS16: the threshold offsets of every (site, pattern)
   l.off_gaddr = take(p->model == PA_MODEL_GAUSS16 ? rows * pa::kRealPatterns * 2 : 0);
   l.total = o;
@@ -666,23 +668,31 @@ constexpr size_t kEvalPoolLevels = 512;
 // 64 bisection halvings keeping the lower end (pa_choose_beta).
 int choose_from_hist(pa_instance* in, double eps_target, double beta_max, double* beta_next) {
   if (in->dev.model == pa::kModelReal) {
-    // the same bisection on the device (weights of every replica): 66
-    // evaluations of the culling fraction, each a weight sum and a culled
-    // mass, decided and advanced by the last workgroup of each
-    const double rem = beta_max - in->beta;
-    pa::RevalArgs a{};
+    // the search on the device (weights of every replica): rounds of two
+    // launches until it has ended, kCullRounds queued before the first look
+    // (eight end most searches; a round that finds it ended costs two
+    // launches that leave at once)
+    pa::CullArgs a{};
     a.E = reinterpret_cast<const long long*>(in->dev.U[in->cur]);
     a.sc = in->dev.sc;
     a.rs = in->dev.rs;
+    a.search = in->dev.rsearch;
     a.rpart = in->dev.rpart;
     a.R = in->dev.R;
     a.capacity = in->dev.capacity;
-    PA_HIP(in, pa::launch_real_bisect_init(in->dev, rem, eps_target, in->stream));
-    for (int e = 0; e < 66; ++e)
-      PA_HIP(in, pa::launch_real_bisect_eval(a, in->meta.rsum[1], in->stream));
-    PA_HIP(in, hipMemcpyAsync(in->h_rs, in->dev.rs, sizeof(pa::RealScalars),
-                              hipMemcpyDeviceToHost, in->stream));
-    PA_HIP(in, hipStreamSynchronize(in->stream));
+    constexpr int kCullRounds = 8, kCullMore = 2;
+    PA_HIP(in, pa::launch_real_cull_start(a, beta_max - in->beta, eps_target, in->stream));
+    // (a round decides at least one halving once the interpolation has ended)
+    for (int done = 0; done < pa::kCullInterp + pa::kCullHalvings + kCullRounds;) {
+      const int n = done ? kCullMore : kCullRounds;
+      for (int r = 0; r < n; ++r)
+        PA_HIP(in, pa::launch_real_cull_round(a, in->meta.rsum[1], in->stream));
+      done += n;
+      PA_HIP(in, hipMemcpyAsync(in->h_rs, in->dev.rs, sizeof(pa::RealScalars),
+                                hipMemcpyDeviceToHost, in->stream));
+      PA_HIP(in, hipStreamSynchronize(in->stream));
+      if (in->h_rs->result != 0) break;
+    }
     const int32_t res = in->h_rs->result;
     if (res == -1) return PA_ESCHEDULE;
     if (res == 1) {
@@ -1254,6 +1264,7 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
   P.rthr32 = real ? reinterpret_cast<uint32_t*>(w + l.off_rthr32) : nullptr;
   P.rs = reinterpret_cast<pa::RealScalars*>(w + l.off_rs);
   P.rpart = real ? reinterpret_cast<pa::RealPartial*>(w + l.off_rpart) : nullptr;
+  P.rsearch = real ? reinterpret_cast<pa::RealSearch*>(w + l.off_rsearch) : nullptr;
   in->d_pops = reinterpret_cast<DevPop*>(w + l.off_pops);
   in->d_meta = reinterpret_cast<MetaU32*>(w + l.off_meta);
   MetaU32& mt = in->meta;

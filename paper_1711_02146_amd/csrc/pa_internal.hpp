@@ -17,6 +17,9 @@
 #include <cstddef>
 #include <cstdint>
 
+#define PA_HD __host__ __device__
+#include "pa_search.hpp"
+
 namespace pa {
 
 // Philox stream tags (fourth counter word): one per use of the generator.
@@ -57,9 +60,9 @@ constexpr uint32_t kRealPatterns = 64;  // patterns y per site
 // entries it never uses.
 constexpr uint32_t kPatternPadRows = 64;
 // Workgroups of the kModelReal weight reductions (grid-stride over the
-// replicas), one per CU: measured at L=10, R=5e5, an evaluation of the
-// bisection takes 17 us on 256 workgroups, 21 us on 128 and 29 us on 1024
-// (each workgroup's arrival costs a device-scope fence and atomic).
+// replicas), one per CU: a reduction of three sums over R = 5e5 words takes 17
+// us on 256 workgroups, 21 us on 128 and 29 us on 1024 (each workgroup's arrival
+// costs a device-scope fence and atomic).
 constexpr uint32_t kRealSumBlocks = 256;
 constexpr int kGaussKMax = 127;
 constexpr int kGaussDEMax = 2 * 6 * kGaussKMax;  // largest |dE16| of one flip
@@ -141,14 +144,19 @@ struct RealScalars {
   uint32_t done;               // workgroups arrived at the current reduction
   double S;                    // sum of the weights of dbeta (Eq. 2, fixed point, rounded)
   double eps;                  // culled fraction (Sec. III.C) of the last copy-count pass
-  double dbeta;                // the step the bisection evaluates next
-  double lo, hi;               // bisection interval
-  double rem, target;          // remaining range and culling target of the bisection
-  uint32_t phase;              // evaluations the bisection has finished
+  double lo;                   // end of the constant-culling search: its lower end
   int32_t result;              // 0 running, 1 whole range, 2 bisected (lo), -1 impossible
-  uint32_t pad[4];
+  uint32_t pad;
 };
-static_assert(sizeof(RealScalars) == 112, "RealScalars is 112 bytes");
+static_assert(sizeof(RealScalars) == 64, "RealScalars is 64 bytes");
+
+// State of the constant-culling search of a kModelReal population: the search
+// and the sums of the weights at its candidates.
+struct RealSearch {
+  CullSearch s;
+  double S[kCullLanes];
+};
+static_assert(sizeof(RealSearch) % 8 == 0, "copied in 8-byte words");
 
 // One workgroup's share of a kModelReal reduction.
 struct RealPartial {
@@ -226,7 +234,9 @@ struct DevPop {
   uint32_t* rthr32;                // kModelReal: min(thr, 2^32 - 1) of the same (cm, y): the
                                    // sweep's table (see pattern_thr)
   RealScalars* rs;                 // kModelReal: scalars of the weight reductions
-  RealPartial* rpart;              // kModelReal: one per workgroup of kBlockCounts slots
+  RealPartial* rpart;              // kModelReal: one per workgroup of kBlockCounts slots, and
+                                   // kCullLanes per reduction workgroup
+  RealSearch* rsearch;             // kModelReal: the constant-culling search
 };
 
 // Parameters of one population for one launch.
@@ -353,24 +363,25 @@ hipError_t launch_real_thresholds(const DevPop& P, double beta, hipStream_t stre
 hipError_t launch_real_stats(const BatchDev& B, const Group& slots, hipStream_t stream);
 // the sum S of the weights exp(-dbeta (E - E_min)) at the step's dbeta into P.rs->S
 hipError_t launch_real_sum(const BatchDev& B, const Group& slots, hipStream_t stream);
-// the constant-culling bisection (Sec. III.C): set up for the remaining range
-// and target, then one evaluation (culled mass at the current candidate, the
-// weight sums of the two that can follow, the decision) per
-// launch_real_bisect_eval; 66 of them finish it (P.rs->result).  Each
-// evaluation runs on `blocks` workgroups (at most kRealSumBlocks: the
-// partials hold three sums each) over one population, whose buffers it takes
-// as arguments, so that its first loads need no descriptor read before them.
-struct RevalArgs {
+// the constant-culling search (Sec. III.C, pa_search.hpp) over the remaining
+// range: its start (after launch_real_stats), then rounds of two launches, the
+// sums of the weights at the round's candidates and their culled masses with
+// the decision, until P.rs->result is set (launches after that leave at once).
+// Each launch runs on `blocks` workgroups (at most kRealSumBlocks) over one
+// population, whose buffers it takes as arguments, so that its first loads need
+// no descriptor read before them.
+struct CullArgs {
   const long long* E;     // energy words of the population's current buffer
   const DevScalars* sc;   // R_tilde
-  RealScalars* rs;        // the search state
-  RealPartial* rpart;     // 3 x blocks partials
+  RealScalars* rs;        // E_min, the arrival counter, the result
+  RealSearch* search;
+  RealPartial* rpart;     // kCullLanes x blocks partials
   uint32_t R;             // target population size
   uint32_t capacity;      // slots per buffer (every slot below it is allocated)
 };
-hipError_t launch_real_bisect_init(const DevPop& P, double rem, double target,
-                                   hipStream_t stream);
-hipError_t launch_real_bisect_eval(const RevalArgs& a, uint32_t blocks, hipStream_t stream);
+hipError_t launch_real_cull_start(const CullArgs& a, double rem, double target,
+                                  hipStream_t stream);
+hipError_t launch_real_cull_round(const CullArgs& a, uint32_t blocks, hipStream_t stream);
 // copy counts of the step (after launch_real_sum at its dbeta): counts, block
 // sums and culled counts as k_counts, and the culled fraction into P.rs->eps
 // (`slots`: at most kRealSumBlocks workgroups, each over every nb-th slot block)

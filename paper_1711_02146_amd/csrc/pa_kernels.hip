@@ -613,7 +613,7 @@ constexpr int pattern_shift() {
 // at bit J + 8m.  With plane k rotated left by k (once per half, xr[k]), the
 // bit that word J needs from plane k sits at J + k + 8m (mod 32): the six
 // masked merges never overlap (k < 8), and one rotation right by J - B moves
-// it to 8m + B + k.  The replica at bit b of a half finds its byte where the
+// it to 8m + B + k.  The replica at bit b of a half finds its byte where
 // plane_byte says.
 template <int J, int B>
 __device__ __forceinline__ uint32_t pattern_word(const uint32_t (&xr)[6]) {
@@ -2420,15 +2420,16 @@ hipError_t launch_real_sum(const BatchDev& B, const Group& g, hipStream_t stream
   return hipGetLastError();
 }
 
-hipError_t launch_real_bisect_init(const DevPop& P, double rem, double target,
-                                   hipStream_t stream) {
-  hipLaunchKernelGGL(k_rbisect_init, dim3(1), dim3(64), 0, stream, P, rem, target);
+hipError_t launch_real_cull_start(const CullArgs& a, double rem, double target,
+                                  hipStream_t stream) {
+  hipLaunchKernelGGL(k_cull_start, dim3(1), dim3(64), 0, stream, a, rem, target);
   return hipGetLastError();
 }
 
-hipError_t launch_real_bisect_eval(const RevalArgs& a, uint32_t blocks, hipStream_t stream) {
+hipError_t launch_real_cull_round(const CullArgs& a, uint32_t blocks, hipStream_t stream) {
   if (!blocks) return hipSuccess;
-  hipLaunchKernelGGL(k_reval, dim3(blocks), dim3(kBlockCounts), 0, stream, a);
+  hipLaunchKernelGGL(k_cull<false>, dim3(blocks), dim3(kBlockCounts), 0, stream, a);
+  hipLaunchKernelGGL(k_cull<true>, dim3(blocks), dim3(kBlockCounts), 0, stream, a);
   return hipGetLastError();
 }
 
