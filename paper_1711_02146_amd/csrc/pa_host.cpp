@@ -565,9 +565,19 @@ double culled_fraction(const EpsLevels& lv, double dbeta, double* w) {
   return acc / (double)lv.R;
 }
 
+// culled_fraction at a step of 0, bit for bit: every weight is 1.
+double culled_fraction_0(const EpsLevels& lv) {
+  double S = 0.0;
+  for (size_t i = 0; i < lv.n; ++i) S = S + lv.cnt[i];
+  const double tau = (double)lv.R / S;
+  double acc = 0.0;
+  if (tau < 1.0)
+    for (size_t i = 0; i < lv.n; ++i) acc = acc + lv.cnt[i] * (1.0 - tau);
+  return acc / (double)lv.R;
+}
+
 // Host threads that evaluate culling fractions beside the calling thread, for
-// the speculative bisection below: kEvalHelpers workers (a round evaluates
-// the candidates of kEvalDepth halvings), started on first use
+// the rounds of the search below: kEvalHelpers workers, started on first use
 // and kept for the life of the process (never destroyed, so that process exit
 // does not wait on them).  A round hands out one candidate per worker, the
 // caller evaluates its own, and waits until every worker has finished.
@@ -575,9 +585,7 @@ double culled_fraction(const EpsLevels& lv, double dbeta, double* w) {
 // microseconds apart), then sleep until the next.  One search uses the pool
 // at a time; a search that finds it busy, or runs in a process forked after
 // the workers started, evaluates its candidates itself.
-constexpr int kEvalDepth = 3;                      // halvings per round
-constexpr int kEvalLanes = (1 << kEvalDepth) - 1;  // candidates per round
-constexpr int kEvalHelpers = kEvalLanes - 1;
+constexpr int kEvalHelpers = pa::kCullLanes - 1;
 constexpr long kEvalSpin = 1l << 13;  // pause loops before a worker sleeps (tens of microseconds)
 
 class EvalPool {
@@ -589,7 +597,7 @@ class EvalPool {
     return pool && pool->started_ == kEvalHelpers && pool->pid_ == getpid() ? pool : nullptr;
   }
   std::mutex& busy() { return busy_; }
-  // out[k] = culled_fraction(lv, x[k]) for k < n (n <= kEvalLanes); the
+  // out[k] = culled_fraction(lv, x[k]) for k < n (n <= kCullLanes); the
   // caller takes x[0] itself.  Call with busy() held.
   void run(const EpsLevels& lv, const double* x, double* out, int n) {
     lv_ = &lv;
@@ -659,8 +667,9 @@ class EvalPool {
   std::vector<double> own_;
 };
 
-// Occupied levels from which the search uses the worker threads; below it
-// one evaluation costs less than handing it out.
+// Occupied levels from which the search uses the worker threads (about nine
+// rounds of an evaluation each, 7 ns a level, and a hand-out of some 5 us);
+// below it the 26 or so evaluations of the serial search cost less.
 constexpr size_t kEvalPoolLevels = 512;
 
 // The constant-culling step of Sec. III.C on the histogram in in->h_hist:
@@ -723,70 +732,38 @@ int choose_from_hist(pa_instance* in, double eps_target, double beta_max, double
   const EpsLevels lvs{arg.data(), cnt.data(), arg.size(), R};
   static thread_local std::vector<double> w;
   w.resize(lvs.n);
-  auto eps_of = [&](double dbeta) { return culled_fraction(lvs, dbeta, w.data()); };
-  const double rem = beta_max - in->beta;
-  // 64 halvings of [0, rem], keeping the lower end (eps(lo) <= target).
-  // With many occupied levels the worker threads evaluate kEvalDepth
-  // halvings' candidates at once: the candidate (lo + (hi - lo)/2) and those
-  // of the halvings after it on either outcome, each formed from the (lo, hi)
-  // the sequential search would hold there, so that lo takes the same bits.
+  // The end point of the 64 halvings of [0, beta_max - beta] (pa_search.hpp)
+  // in about 26 evaluations, or, with many occupied levels, nine rounds of
+  // seven on the worker threads: a step took 66 evaluations, or 23 rounds.
+  // The first guess is the crossing of a Gaussian of the levels' mean: a step
+  // dbeta culls sigma dbeta / sqrt(2 pi), the mean lies sigma sqrt(2 ln R~)
+  // above the lowest of R~ energies.
   EvalPool* pool = lvs.n >= kEvalPoolLevels ? EvalPool::get() : nullptr;
   std::unique_lock<std::mutex> held;
   if (pool) {
     held = std::unique_lock<std::mutex>(pool->busy(), std::try_to_lock);
     if (!held.owns_lock()) pool = nullptr;
   }
-  double e0, erem;
-  if (pool) {
-    const double x[2] = {0.0, rem};
-    double out[2];
-    pool->run(lvs, x, out, 2);
-    e0 = out[0];
-    erem = out[1];
-  } else {
-    e0 = eps_of(0.0);
-    erem = e0 > eps_target ? 0.0 : eps_of(rem);
+  double total = 0.0, mean_d = 0.0;
+  for (size_t i = 0; i < lvs.n; ++i) {
+    total += lvs.cnt[i];
+    mean_d += lvs.cnt[i] * lvs.arg[i];
   }
-  if (e0 > eps_target) return PA_ESCHEDULE;
-  if (erem <= eps_target) {
-    *beta_next = beta_max;
-    return PA_OK;
+  if (lvs.n > 0) mean_d /= total;
+  pa::CullSearch s;
+  pa::cull_eta(s, mean_d * 1.001, (double)lvs.n, total / (double)R);
+  pa::cull_start(s, beta_max - in->beta, eps_target, lvs.n > 0 ? culled_fraction_0(lvs) : 0.0,
+                 mean_d > 0.0 ? eps_target * 2.5 * std::sqrt(2.0 * std::log(total + 2.0)) / mean_d
+                              : beta_max - in->beta,
+                 pool ? pa::kCullLanes : pa::kCullSerial);
+  while (s.result == 0) {
+    if (pool) pool->run(lvs, s.x, s.e, s.n);
+    else
+      for (int k = 0; k < s.n; ++k) s.e[k] = culled_fraction(lvs, s.x[k], w.data());
+    pa::cull_advance(s);
   }
-  double lo = 0.0, hi = rem;
-  if (!pool) {
-    for (int it = 0; it < 64; ++it) {
-      const double mid = lo + 0.5 * (hi - lo);
-      if (eps_of(mid) <= eps_target) lo = mid;
-      else hi = mid;
-    }
-  } else {
-    // the subtree of (lo, hi): node k has children 2k + 1 (not taken: hi =
-    // its candidate) and 2k + 2 (taken: lo = its candidate)
-    for (int left = 64; left > 0;) {
-      const int depth = left < kEvalDepth ? left : kEvalDepth, n = (1 << depth) - 1;
-      double nlo[kEvalLanes], nhi[kEvalLanes], x[kEvalLanes], e[kEvalLanes];
-      nlo[0] = lo;
-      nhi[0] = hi;
-      for (int k = 0; k < n; ++k) {
-        x[k] = nlo[k] + 0.5 * (nhi[k] - nlo[k]);
-        if (2 * k + 2 < n) {
-          nlo[2 * k + 1] = nlo[k];
-          nhi[2 * k + 1] = x[k];
-          nlo[2 * k + 2] = x[k];
-          nhi[2 * k + 2] = nhi[k];
-        }
-      }
-      pool->run(lvs, x, e, n);
-      for (int d = 0, k = 0; d < depth; ++d) {
-        const bool ok = e[k] <= eps_target;
-        if (ok) lo = x[k];
-        else hi = x[k];
-        k = 2 * k + (ok ? 2 : 1);
-      }
-      left -= depth;
-    }
-  }
-  *beta_next = in->beta + lo;
+  if (s.result == -1) return PA_ESCHEDULE;
+  *beta_next = s.result == 1 ? beta_max : in->beta + s.lo;
   return PA_OK;
 }
 

@@ -222,7 +222,7 @@ PA_HD inline void cull_advance(CullSearch& s) {
     for (int k = 0; k < kCullLanes; ++k) {
       const int q = wide ? k - 3 : k - 1;  // -3..3, or -1, 0, 1
       const int m = q < 0 ? -q : q;
-      const double f = !wide ? (first_round ? 2e-2 : 1e-3)
+      const double f = !wide ? (first_round ? 5e-2 : s.round == 2 ? 1e-4 : 1e-7)
                        : m == 3 ? (first_round ? 0.12 : 1e-2)
                        : m == 2 ? (first_round ? 4e-3 : 1e-5)
                                 : (first_round ? 5e-5 : 1e-9);
