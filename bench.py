@@ -741,8 +741,8 @@ def kernel_src_sha256():
     import hashlib
 
     h = hashlib.sha256()
-    for name in ("pa_kernels.hip", "pa_sweep_pm.inc", "pa_real_kernels.inc", "pa_search.hpp",
-                 "pa_internal.hpp"):
+    for name in ("pa_kernels.hip", "pa_sweep_pm.inc", "pa_sweep_gauss.inc", "pa_real_kernels.inc",
+                 "pa_search.hpp", "pa_internal.hpp"):
         with open(os.path.join(ROOT, "paper_1711_02146_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

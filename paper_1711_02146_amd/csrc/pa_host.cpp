@@ -310,8 +310,7 @@ pa::PopStep plain_step(uint32_t cur) {
 // that every block is the member's).
 pa::Group sweep_group(const pa_instance* in, uint32_t split) {
   return group_of(in, in->d_meta->tiles,
-                  pa::blocks_sweep(in->dev.capacity,
-                                   pa::sweep_tiles(in->dev.model, in->dev.L, split)));
+                  pa::sweep_blocks(in->dev.model, in->dev.L, split, in->dev.capacity));
 }
 
 // Sweep launch of one instance (its size after any pending copy sets the

@@ -14,6 +14,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 
@@ -105,6 +106,21 @@ constexpr uint32_t kPmPacked = 1;
 __host__ __device__ constexpr uint32_t pm_waves(uint32_t split) { return split == 8 ? 8 : 4; }
 __host__ __device__ constexpr uint32_t pm_tiles(uint32_t L, uint32_t split) {
   return split != kPmPacked ? 1 : L <= 6 ? 4 : L == 8 ? 2 : 1;
+}
+
+// The Gaussian sweep with its table in LDS (k_sweep_gauss, L <= 10): waves and tiles
+// per workgroup, bytes of a wave's plane area (16 sites x 64 replicas, one byte
+// each), waves per SIMD that its registers are budgeted for (as many as the LDS
+// lets run, at most five), and the workgroups that fill 256 CUs.
+constexpr uint32_t kGaussLds = 2;
+constexpr uint32_t kGaussPlaneBytes = 16 * 64;
+__host__ __device__ constexpr uint32_t gauss_waves(uint32_t L) { return L == 10 ? 16 : 8; }
+__host__ __device__ constexpr uint32_t gauss_tiles(uint32_t L) {
+  return L == 4 ? 8 : L == 6 ? 4 : 2;
+}
+constexpr int kGaussWavesPerEu = 4;
+inline uint32_t gauss_resident(uint32_t L) {
+  return 256 * 4 * (uint32_t)kGaussWavesPerEu / gauss_waves(L);
 }
 
 // A site for one 32-replica half of a lane in phase 1 of the +-J colour pass:
@@ -322,8 +338,8 @@ hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream)
 // k_scan and k_scatter of one population in one launch (g: its slot blocks)
 hipError_t launch_scan_scatter(const BatchDev& B, const Group& g, hipStream_t stream);
 // sweep launch over the populations of one (layout, L, model) group in the form
-// `split` (4 or 8 waves per workgroup); g's blocks are blocks_sweep(capacity,
-// sweep_tiles(model, L, split))
+// `split` (see sweep_form); g's blocks are sweep_blocks (one population) or
+// blocks_sweep(capacity, sweep_tiles(model, L, split)) per population
 hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint32_t L,
                         uint32_t split, uint32_t model, hipStream_t stream);
 hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream);
@@ -401,7 +417,12 @@ inline uint32_t blocks_sweep(uint32_t capacity, uint32_t per_block) {
 }
 // Tiles per workgroup of a sweep launch.
 inline uint32_t sweep_tiles(uint32_t model, uint32_t L, uint32_t split) {
-  return model == kModelPm ? pm_tiles(L, split) : 1;
+  return model == kModelPm ? pm_tiles(L, split) : split == kGaussLds ? gauss_tiles(L) : 1;
+}
+// Workgroups of a sweep launch of one population.
+inline uint32_t sweep_blocks(uint32_t model, uint32_t L, uint32_t split, uint32_t capacity) {
+  const uint32_t all = blocks_sweep(capacity, sweep_tiles(model, L, split));
+  return model != kModelPm && split == kGaussLds ? std::min(all, gauss_resident(L)) : all;
 }
 // Waves per workgroup of a sweep launch over `tiles` tiles of linear size L, from
 // timings on MI355X (10 sweeps, beta = 1).
@@ -412,18 +433,24 @@ inline uint32_t sweep_tiles(uint32_t model, uint32_t L, uint32_t split) {
 // waves still have a full chunk each (L = 12, 3125 tiles 1.152 / 1.175; L = 16,
 // 1563 tiles 1.52 / 1.92); at L = 6 four are never slower (157 tiles 0.046 /
 // 0.046, 1563 tiles 0.186 / 0.132).
-// Gaussian models: eight from L = 10 up, and on smaller lattices while the launch
-// is too small to fill the chip with four (fewer than 256 (L - 2) tiles: 512 at
-// L = 4, 1024 at L = 6, 1536 at L = 8); four otherwise, where more resident tiles
-// per CU pay.
+// Gaussian models, L <= 10: four (the form with its table in LDS, which fills a
+// CU with one or two workgroups of several tiles) once the launch fills the chip
+// that way, the eight-wave kernel below (ms per launch of 10 sweeps, table in LDS /
+// eight waves, real couplings: L = 4, 512 tiles 0.054 / 0.049, 768 tiles 0.055 /
+// 0.066; L = 6, 512 tiles 0.100 / 0.082, 768 tiles 0.101 / 0.108; L = 8, 256 tiles
+// 0.113 / 0.083, 512 tiles 0.118 / 0.139; L = 10, 256 tiles 0.152 / 0.133, 384
+// tiles 0.156 / 0.221, 7813 tiles 2.27 / 3.03).  From L = 12 up, where the table
+// does not fit, eight.
 inline uint32_t sweep_split_default(uint32_t model, uint32_t L, uint64_t tiles) {
   if (model == kModelPm) {
     const uint64_t few = L == 4 ? 512 : L == 6 ? 0 : L == 8 ? 256 : 768;
     return L >= 12 || tiles < few ? 8u : 4u;
   }
-  return (L >= 10 || tiles < 256ull * (L - 2)) ? 8u : 4u;
+  const uint64_t few = L <= 6 ? 640 : L == 8 ? 384 : 320;
+  return L >= 12 || tiles < few ? 8u : 4u;
 }
-// The kernel form of a launch with `split` waves per workgroup: +-J on four waves
+// The kernel form of a launch with `split` waves per workgroup.  Gaussian models on
+// four waves, L <= 10: the kernel with its table in LDS.  +-J on four waves
 // packs several tiles per workgroup where there are enough of them (ms per
 // launch packed / one tile per workgroup: L = 4, 313 tiles 0.044 / 0.047, 7813
 // tiles 0.157 / 0.333; L = 6, 782 tiles 0.104 / 0.086, 1563 tiles 0.128 / 0.132,
@@ -431,7 +458,8 @@ inline uint32_t sweep_split_default(uint32_t model, uint32_t L, uint64_t tiles) 
 // 0.382, 7813 tiles 0.824 / 0.873).
 inline uint32_t sweep_form(uint32_t model, uint32_t L, uint32_t split, uint64_t tiles) {
   const uint64_t enough = L == 4 ? 0 : L == 6 ? 1500 : 3200;
-  return model == kModelPm && split == 4 && L <= 8 && tiles >= enough ? kPmPacked : split;
+  if (model != kModelPm) return split == 4 && L <= 10 ? kGaussLds : split;
+  return split == 4 && L <= 8 && tiles >= enough ? kPmPacked : split;
 }
 // The form a launch uses: sweep_form of the autotuner's choice for (model,
 // layout, L, size class of `tiles`) when one was measured in this process, else

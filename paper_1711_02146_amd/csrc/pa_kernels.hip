@@ -1551,7 +1551,8 @@ __global__ __launch_bounds__(kBlockCounts) void k_scan_scatter(BatchDev B, Group
 //
 // Register budget: as many waves per SIMD as fit without spilling to scratch
 // memory (seven up to L = 8, six at 10, five at 12 and 14, four at 16).  (+-J
-// populations: k_sweep_pm.)
+// populations: k_sweep_pm.  Gaussian ones up to L = 10 that fill the chip:
+// k_sweep_gauss; this kernel then takes the smaller launches, on eight waves.)
 template <int L, int M>
 constexpr int sweep_min_waves_per_eu() {
   static_assert(M == (int)kModelGauss16 || M == (int)kModelReal, "Gaussian models");
@@ -1684,6 +1685,8 @@ __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_swee
 
 // the +-J sweep kernel
 #include "pa_sweep_pm.inc"
+// the Gaussian sweep kernel with its table in LDS
+#include "pa_sweep_gauss.inc"
 
 // The energy word recomputed from the stored spins of buffer cur (after an
 // import; for kModelGauss16 also after the initial spins are drawn), or, with
@@ -2101,28 +2104,38 @@ __global__ __launch_bounds__(256) void k_probe_philox(uint32_t* out, uint32_t ca
 template <int LAYOUT, int L>
 void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t model,
                     hipStream_t stream) {
-  // after the tile image and the reduction area: the Gaussian threshold table,
-  // or the +-J plane areas (one per wave)
-  // after the tile image: the reduction area and the Gaussian threshold table,
-  // or the +-J plane areas (one per wave; the reduction area lies over them)
+  // k_sweep, after the tile image: the plane areas (one per wave; the reduction
+  // area lies over them) and the quantised threshold table
   const size_t after = model == kModelGauss16
                            ? (size_t)kPlaneAreaBytes * split + (size_t)(kGaussDEMax + 1) * 8
                            : (size_t)kPlaneAreaBytes * split;
   static_assert(kPlaneAreaBytes >= 8 * 64, "the reduction area lies over the plane areas");
   const size_t lds = (size_t)L * L * L * 8 + after;
+  if constexpr (L <= 10) {
+    if (model != kModelPm && split == kGaussLds) {
+      const dim3 grid(g.blocks), block(64 * gauss_waves(L));
+      if (model == kModelReal)
+        hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelReal>), grid, block,
+                           GaussShape<L>::bytes, stream, B, g);
+      else
+        hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelGauss16>), grid, block,
+                           GaussShape<L>::bytes, stream, B, g);
+      return;
+    }
+  }
   if (model == kModelReal) {
-    if (split == 8)
+    if (split == 8 || L <= 10)
       hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelReal>), dim3(g.blocks), dim3(64 * 8), lds,
                          stream, B, g);
     else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelReal>), dim3(g.blocks), dim3(64 * 4), lds,
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, L <= 10 ? 8 : 4, kModelReal>), dim3(g.blocks), dim3(64 * 4), lds,
                          stream, B, g);
   } else if (model == kModelGauss16) {
-    if (split == 8)
+    if (split == 8 || L <= 10)
       hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelGauss16>), dim3(g.blocks), dim3(64 * 8), lds,
                          stream, B, g);
     else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelGauss16>), dim3(g.blocks), dim3(64 * 4), lds,
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, L <= 10 ? 8 : 4, kModelGauss16>), dim3(g.blocks), dim3(64 * 4), lds,
                          stream, B, g);
   } else {
     const size_t lds_pm = kPmImage + (size_t)L * L * L * 8 * pm_tiles(L, split) +
@@ -2309,8 +2322,10 @@ hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream)
 hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint32_t L,
                         uint32_t split, uint32_t model, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
-  if (split != 4 && split != 8 && !(split == kPmPacked && model == kModelPm && L <= 8))
+  if (split != 4 && split != 8 && !(split == kPmPacked && model == kModelPm && L <= 8) &&
+      !(split == kGaussLds && model != kModelPm && L <= 10 && g.n == 1))
     return hipErrorInvalidValue;
+  if (split == 4 && model != kModelPm && L <= 10) return hipErrorInvalidValue;
   if (layout == 2) {
     PA_L_SWITCH_S(launch_sweep_l, 2)
   } else {
