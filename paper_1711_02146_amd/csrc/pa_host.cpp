@@ -1642,6 +1642,12 @@ int pa_link_overlap_hist_noalloc(pa_instance* a, pa_instance* b, uint32_t nbins,
   return PA_OK;
 }
 
+// Replicas whose canonical spins (one byte each) fit in a spin buffer: a multiple
+// of 32, as the capacity is one of 256.
+static uint32_t staged_replicas(const DevPop& P) {
+  return P.layout == PA_LAYOUT_BITPACK64 ? P.capacity / 8 : P.capacity;
+}
+
 int pa_export_state(pa_instance* in, int8_t* spins_host, uint32_t* U_host, uint32_t* family_host,
                     uint32_t* R_tilde) {
   if (int rc0 = enter(in)) return rc0;
@@ -1660,26 +1666,17 @@ int pa_export_state(pa_instance* in, int8_t* spins_host, uint32_t* U_host, uint3
   if (family_host && R)
     PA_HIP(in, hipMemcpy(family_host, P.fam[in->cur], (size_t)R * 4, hipMemcpyDeviceToHost));
   if (spins_host && R) {
-    const uint32_t N = P.N, tiles = (R + 63) / 64;
-    const size_t tile_bytes = P.layout == PA_LAYOUT_BITPACK64 ? (size_t)N * 8 : (size_t)N * 64;
-    std::vector<uint8_t> raw((size_t)tiles * tile_bytes);
-    PA_HIP(in, hipMemcpy(raw.data(), P.spins[in->cur], raw.size(), hipMemcpyDeviceToHost));
-    for (uint32_t r = 0; r < R; ++r) {
-      const uint32_t tile = r >> 6, lane = r & 63u;
-      int8_t* dst = spins_host + (size_t)r * N;
-      for (uint32_t s = 0; s < N; ++s) {
-        const uint32_t cm = in->cm_of_site[s];
-        bool neg;
-        if (P.layout == PA_LAYOUT_BITPACK64) {
-          uint64_t wd;
-          std::memcpy(&wd, raw.data() + ((size_t)tile * N + cm) * 8, 8);
-          neg = (wd >> lane) & 1ull;
-        } else {
-          neg = (int8_t)raw[((size_t)tile * N + cm) * 64 + lane] < 0;
-        }
-        dst[s] = neg ? (int8_t)-1 : (int8_t)1;
-      }
+    // the population's other buffer is free between calls: converted there and
+    // copied out, as many replicas at a time as it holds
+    const uint32_t per = staged_replicas(P);
+    int8_t* const stage = static_cast<int8_t*>(P.spins[in->cur ^ 1u]);
+    for (uint32_t r0 = 0; r0 < R; r0 += per) {
+      const uint32_t rows = std::min(per, R - r0);
+      PA_HIP(in, pa::launch_export_spins(P, in->cur, stage, R, r0, r0 + rows, in->stream));
+      PA_HIP(in, hipMemcpyAsync(spins_host + (size_t)r0 * P.N, stage, (size_t)rows * P.N,
+                                hipMemcpyDeviceToHost, in->stream));
     }
+    PA_HIP(in, hipStreamSynchronize(in->stream));
   }
   return PA_OK;
 }
@@ -1711,27 +1708,27 @@ int pa_import_state(pa_instance* in, const int8_t* spins_host, const uint32_t* f
     if (family_host[i] >= P.R) return PA_EINVAL;
     if (i && family_host[i] < family_host[i - 1]) return PA_EINVAL;  // labels must be sorted
   }
-  const uint32_t N = P.N, tiles = (R_tilde + 63) / 64;
-  const size_t tile_bytes = P.layout == PA_LAYOUT_BITPACK64 ? (size_t)N * 8 : (size_t)N * 64;
-  std::vector<uint8_t> raw((size_t)tiles * tile_bytes, 0);
-  for (uint32_t r = 0; r < R_tilde; ++r) {
-    const uint32_t tile = r >> 6, lane = r & 63u;
-    const int8_t* s = spins_host + (size_t)r * N;
-    for (uint32_t site = 0; site < N; ++site) {
-      if (s[site] != 1 && s[site] != -1) return PA_EINVAL;
-      const uint32_t cm = in->cm_of_site[site];
-      if (P.layout == PA_LAYOUT_BITPACK64) {
-        if (s[site] < 0) raw[((size_t)tile * N + cm) * 8 + (lane >> 3)] |= (uint8_t)(1u << (lane & 7));
-      } else {
-        raw[((size_t)tile * N + cm) * 64 + lane] = (uint8_t)s[site];
-      }
-    }
-  }
+  // every spin is +1 or -1: s + 1 is 2 or 0
+  const size_t n_spins = (size_t)R_tilde * P.N;
+  uint8_t other = 0;
+  for (size_t i = 0; i < n_spins; ++i) other |= (uint8_t)(spins_host[i] + 1) & (uint8_t)~2u;
+  if (other != 0) return PA_EINVAL;
   int rc = materialize(in);  // drop nothing silently: finish a pending copy first
   if (rc) return rc;
   PA_HIP(in, hipStreamSynchronize(in->stream));
-  if (!raw.empty())
-    PA_HIP(in, hipMemcpy(P.spins[in->cur], raw.data(), raw.size(), hipMemcpyHostToDevice));
+  // staged in the population's other buffer and converted, as many replicas at a
+  // time as it holds; the last slots of the last tile are cleared
+  const uint32_t slots = (R_tilde + 63) / 64 * 64, per = staged_replicas(P);
+  int8_t* const stage = static_cast<int8_t*>(P.spins[in->cur ^ 1u]);
+  for (uint32_t r0 = 0; r0 < slots; r0 += per) {
+    const uint32_t r1 = std::min(r0 + per, slots);
+    if (r0 < R_tilde)
+      PA_HIP(in, hipMemcpyAsync(stage, spins_host + (size_t)r0 * P.N,
+                                (size_t)(std::min(r1, R_tilde) - r0) * P.N, hipMemcpyHostToDevice,
+                                in->stream));
+    PA_HIP(in, pa::launch_import_spins(P, in->cur, stage, R_tilde, r0, r1, in->stream));
+  }
+  PA_HIP(in, hipStreamSynchronize(in->stream));
   if (R_tilde)
     PA_HIP(in, hipMemcpy(P.fam[in->cur], family_host, (size_t)R_tilde * 4, hipMemcpyHostToDevice));
   DevScalars sc{};

@@ -325,6 +325,12 @@ constexpr int kProbeValuOpsPerIter = 32;
 hipError_t launch_probe_valu(uint32_t* out, uint32_t iters, uint32_t form, hipStream_t stream);
 hipError_t launch_probe_philox(uint32_t* out, uint32_t calls, hipStream_t stream);
 hipError_t launch_init(const DevPop& P, uint32_t cur, hipStream_t stream);
+// the slots r0 .. r1 - 1 (multiples of 32), [replica][site] int8 in device memory,
+// from buffer cur (R: replicas of the population) and back into it
+hipError_t launch_export_spins(const DevPop& P, uint32_t cur, int8_t* out, uint32_t R,
+                               uint32_t r0, uint32_t r1, hipStream_t stream);
+hipError_t launch_import_spins(const DevPop& P, uint32_t cur, const int8_t* in, uint32_t R,
+                               uint32_t r0, uint32_t r1, hipStream_t stream);
 hipError_t launch_zero_acc(const BatchDev& B, const Group& per_pop, hipStream_t stream);
 hipError_t launch_hist(const BatchDev& B, const Group& g, uint32_t max_levels, bool post,
                        hipStream_t stream);

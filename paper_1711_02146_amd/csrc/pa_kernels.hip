@@ -2093,6 +2093,68 @@ __global__ __launch_bounds__(256) void k_probe_philox(uint32_t* out, uint32_t ca
   out[gid] = acc;
 }
 
+// ---------------------------------------------------------------------------
+// The canonical host layout ([replica][site] int8, sites in lexicographic order)
+// of the slots r0 .. r1 - 1 (multiples of 32: whole halves of a tile's words), and
+// back.  One workgroup per tile, lane = replica,
+// eight sites per wave and step: a site's words (or its 64 bytes) are read whole,
+// a lane's eight bytes written together (N is a multiple of 8).  A chunk of an
+// export or import is bound by its copy over the host link; the conversion on
+// the host that these kernels replace took 100 ms per 51 MB (L = 8, R = 1e5),
+// these take 0.1 ms (out) and 0.2 ms (in); a checkpoint out and in 193 -> 8.3 ms.
+// ---------------------------------------------------------------------------
+template <int LAYOUT>
+__global__ __launch_bounds__(256) void k_export_spins(const void* spins, const uint16_t* cm_of_site,
+                                                      int8_t* out, uint32_t N, uint32_t R,
+                                                      uint32_t r0, uint32_t r1) {
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const uint32_t tile = r0 / 64 + blockIdx.x, r = tile * 64 + lane;
+  if (r < r0 || r >= min(r1, R)) return;
+  int8_t* const dst = out + (size_t)(r - r0) * N;
+  for (uint32_t s0 = 8 * wave; s0 < N; s0 += 32) {
+    uint32_t v[2] = {0u, 0u};
+#pragma unroll
+    for (uint32_t i = 0; i < 8; ++i) {
+      const size_t site = (size_t)tile * N + cm_of_site[s0 + i];
+      bool neg;
+      if constexpr (LAYOUT == 2)
+        neg = (static_cast<const unsigned long long*>(spins)[site] >> lane) & 1ull;
+      else
+        neg = static_cast<const int8_t*>(spins)[site * 64 + lane] < 0;
+      v[i / 4] |= (neg ? 0xFFu : 1u) << (8 * (i & 3u));
+    }
+    *reinterpret_cast<uint2*>(dst + s0) = make_uint2(v[0], v[1]);
+  }
+}
+
+// (slots of the last tile past R are cleared)
+template <int LAYOUT>
+__global__ __launch_bounds__(256) void k_import_spins(void* spins, const uint16_t* cm_of_site,
+                                                      const int8_t* in, uint32_t N, uint32_t R,
+                                                      uint32_t r0, uint32_t r1) {
+  const uint32_t lane = lane_id(), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / 64);
+  const uint32_t tile = r0 / 64 + blockIdx.x, r = tile * 64 + lane;
+  if (r < r0 || r >= r1) return;  // whole halves of the wave
+  const bool valid = r < R;
+  const int8_t* const src = in + (size_t)(r - r0) * N;
+  for (uint32_t s0 = 8 * wave; s0 < N; s0 += 32) {
+    uint2 v = make_uint2(0u, 0u);
+    if (valid) v = *reinterpret_cast<const uint2*>(src + s0);
+#pragma unroll
+    for (uint32_t i = 0; i < 8; ++i) {
+      const size_t site = (size_t)tile * N + cm_of_site[s0 + i];
+      const int8_t s = (int8_t)((i < 4 ? v.x : v.y) >> (8 * (i & 3u)));
+      if constexpr (LAYOUT == 2) {
+        const unsigned long long m = __ballot(s < 0);
+        if ((lane & 31u) == 0)
+          static_cast<uint32_t*>(spins)[2 * site + (lane >> 5)] = (uint32_t)(m >> (lane & 32u));
+      } else {
+        static_cast<int8_t*>(spins)[site * 64 + lane] = s;
+      }
+    }
+  }
+}
+
 // the kernels of the real-coupling model (kModelReal)
 #include "pa_real_kernels.inc"
 
@@ -2226,6 +2288,30 @@ hipError_t launch_init(const DevPop& P, uint32_t cur, hipStream_t stream) {
   else
     hipLaunchKernelGGL(k_init<1>, dim3(tiles_of(P.R)), dim3(64), lds, stream, P, cur,
                        P.cm_of_site);
+  return hipGetLastError();
+}
+
+hipError_t launch_export_spins(const DevPop& P, uint32_t cur, int8_t* out, uint32_t R,
+                               uint32_t r0, uint32_t r1, hipStream_t stream) {
+  const uint32_t tiles = tiles_of(r1) - r0 / 64;
+  if (P.layout == 2)
+    hipLaunchKernelGGL(k_export_spins<2>, dim3(tiles), dim3(256), 0, stream, P.spins[cur],
+                       P.cm_of_site, out, P.N, R, r0, r1);
+  else
+    hipLaunchKernelGGL(k_export_spins<1>, dim3(tiles), dim3(256), 0, stream, P.spins[cur],
+                       P.cm_of_site, out, P.N, R, r0, r1);
+  return hipGetLastError();
+}
+
+hipError_t launch_import_spins(const DevPop& P, uint32_t cur, const int8_t* in, uint32_t R,
+                               uint32_t r0, uint32_t r1, hipStream_t stream) {
+  const uint32_t tiles = tiles_of(r1) - r0 / 64;
+  if (P.layout == 2)
+    hipLaunchKernelGGL(k_import_spins<2>, dim3(tiles), dim3(256), 0, stream, P.spins[cur],
+                       P.cm_of_site, in, P.N, R, r0, r1);
+  else
+    hipLaunchKernelGGL(k_import_spins<1>, dim3(tiles), dim3(256), 0, stream, P.spins[cur],
+                       P.cm_of_site, in, P.N, R, r0, r1);
   return hipGetLastError();
 }
 
