@@ -49,7 +49,7 @@ bool batch_layout(uint32_t n_pops, uint32_t n_pairs, uint32_t n_steps, uint32_t 
   // group tables: 3 groups of (n pop ids + n + 1 starts), sweep groups
   // (n ids + n + 16 starts), pair groups (n_pairs ids + n_pairs + 2 starts)
   // and the 2 n_pairs pair members
-  l.n_u32 = 3 * (2 * (size_t)n_pops + 1) + (2 * (size_t)n_pops + 16) + 4 * (size_t)n_pairs + 2;
+  l.n_u32 = 4 * (2 * (size_t)n_pops + 1) + (2 * (size_t)n_pops + 16) + 4 * (size_t)n_pairs + 2;
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -80,7 +80,7 @@ struct pa_batch {
   BatchLayout lay{};
   pa::BatchDev dev{};
   uint32_t* d_ctr = nullptr;
-  pa::Group g_perpop{}, g_slots{}, g_hist{};
+  pa::Group g_perpop{}, g_slots{}, g_hist{}, g_post{};
   struct SweepGroup {
     uint32_t layout, L;
     uint32_t split;  // waves per tile
@@ -121,13 +121,10 @@ int capture_step(pa_batch* b) {
   PB_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
   bool ok = pa::launch_table(B, b->g_perpop, s) == hipSuccess &&
             pa::launch_counts(B, b->g_slots, s) == hipSuccess &&
-            pa::launch_scan(B, b->g_perpop, s) == hipSuccess &&
-            pa::launch_scatter(B, b->g_slots, s) == hipSuccess;
+            pa::launch_scan_scatter(B, b->g_slots, s) == hipSuccess;
   for (const auto& sg : b->g_sweep)
     ok = ok && pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, s) == hipSuccess;
-  ok = ok && pa::launch_zero_acc(B, b->g_perpop, s) == hipSuccess &&
-       pa::launch_hist(B, b->g_hist, b->max_levels, true, s) == hipSuccess &&
-       pa::launch_family(B, b->g_slots, true, s) == hipSuccess &&
+  ok = ok && pa::launch_hist_family(B, b->g_post, b->max_levels, s) == hipSuccess &&
        pa::launch_record(B, b->g_perpop, s) == hipSuccess;
   for (const auto& pg : b->g_pairs)
     ok = ok && pa::launch_overlap(B, pg.g, b->d_pair_pops, pg.layout, s) == hipSuccess;
@@ -237,7 +234,7 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
       ps.gather = 1;
       ps.cur = b->cur0[p] ^ (s & 1u);
       ps.step = b->step0[p] + s + 1;
-      ps.flags = pa::kStepSticky;
+      ps.flags = pa::kStepSticky | pa::kStepHist;
     }
   }
   // group tables
@@ -249,15 +246,17 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
   };
   std::vector<uint32_t>& u32 = gt.u32;
   uint32_t* const d_u32 = gt.d_base;
-  std::vector<uint32_t> all(n_pops), one(n_pops, 1), slots(n_pops), hist(n_pops);
+  std::vector<uint32_t> all(n_pops), one(n_pops, 1), slots(n_pops), hist(n_pops), post(n_pops);
   for (uint32_t p = 0; p < n_pops; ++p) {
     all[p] = p;
     slots[p] = pa::blocks_slots(pops[p]->dev.capacity);
     hist[p] = pa::blocks_hist(pops[p]->dev.capacity);
+    post[p] = pa::blocks_hist_family(pops[p]->dev.capacity);
   }
   b->g_perpop = add_group(all, one);
   b->g_slots = add_group(all, slots);
   b->g_hist = add_group(all, hist);
+  b->g_post = add_group(all, post);
   std::map<std::pair<uint32_t, uint32_t>, std::vector<uint32_t>> by_kind;
   for (uint32_t p = 0; p < n_pops; ++p) by_kind[{pops[p]->dev.layout, pops[p]->dev.L}].push_back(p);
   for (const auto& kv : by_kind) {

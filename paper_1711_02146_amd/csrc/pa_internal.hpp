@@ -339,15 +339,17 @@ hipError_t launch_counts(const BatchDev& B, const Group& g, hipStream_t stream);
 // the same with the table's occupied range passed by value (single populations)
 hipError_t launch_counts_inline(const BatchDev& B, const Group& g, const InlineTable& t,
                                 hipStream_t stream);
-hipError_t launch_scan(const BatchDev& B, const Group& per_pop, hipStream_t stream);
-hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream);
-// k_scan and k_scatter of one population in one launch (g: its slot blocks)
+// offsets, new sizes and copy maps (g: the populations' slot blocks)
 hipError_t launch_scan_scatter(const BatchDev& B, const Group& g, hipStream_t stream);
 // sweep launch over the populations of one (layout, L, model) group in the form
 // `split` (see sweep_form); g's blocks are sweep_blocks (one population) or
 // blocks_sweep(capacity, sweep_tiles(model, L, split)) per population
 hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint32_t L,
                         uint32_t split, uint32_t model, hipStream_t stream);
+// histogram and family sum of the sets' new populations (g: blocks_hist_family
+// workgroups each)
+hipError_t launch_hist_family(const BatchDev& B, const Group& g, uint32_t max_levels,
+                              hipStream_t stream);
 hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream);
 hipError_t launch_record(const BatchDev& B, const Group& per_pop, hipStream_t stream);
 // overlap histograms of a batch step's pairs (blocks_overlap workgroups each)
@@ -411,6 +413,10 @@ hipError_t launch_real_counts(const BatchDev& B, const Group& slots, hipStream_t
 
 // Blocks each population needs in each kind of launch.
 inline uint32_t blocks_hist(uint32_t capacity) { return (capacity + kHistSlots - 1) / kHistSlots; }
+constexpr uint32_t kFamilyBlocks = 512;  // workgroups of a population that sum its families
+inline uint32_t blocks_hist_family(uint32_t capacity) {
+  return blocks_hist(capacity) + std::min(capacity / kBlockCounts, kFamilyBlocks);
+}
 inline uint32_t blocks_overlap(uint32_t capacity) {
   return (capacity / 64 + kOverlapTiles - 1) / kOverlapTiles;
 }

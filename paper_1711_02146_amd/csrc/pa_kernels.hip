@@ -1053,17 +1053,16 @@ __device__ __forceinline__ void slot_words(const uint32_t* U, uint32_t i0, uint3
 }
 
 // Energy histogram h_j = #{i < R~ : U_i = j} (the sum of Eq. 2 regrouped by
-// integer level), privatised in LDS; each workgroup takes kHistSlots slots.
-__global__ __launch_bounds__(256) void k_hist(BatchDev B, Group G, uint32_t post) {
+// integer level), privatised in LDS; workgroup lb of a population takes its
+// lb-th kHistSlots slots.
+__device__ __forceinline__ void hist_body(const DevPop& P, const PopStep& sp, uint32_t lb,
+                                          uint32_t post) {
   extern __shared__ uint32_t h[];
-  const Member m = member_of(G);
-  const DevPop P = B.pops[m.pop];
-  const PopStep sp = step_of(B, m.pop);
   const uint32_t* U = pick(P.U, post ? sp.cur ^ 1u : sp.cur);
   // the population's flag and size and the thread's slot words read together
   // (every slot below the capacity is allocated), then the flag checked
   const uint32_t dead = P.sc->dead, R = P.sc->R_tilde;
-  const uint32_t i0 = m.lb * kHistSlots, i1 = min(R, i0 + kHistSlots);
+  const uint32_t i0 = lb * kHistSlots, i1 = min(R, i0 + kHistSlots);
   uint32_t u[kHistPer];
   slot_words(U, i0, min(P.capacity, i0 + kHistSlots), u);
   asm volatile("" ::"v"(R));
@@ -1076,6 +1075,11 @@ __global__ __launch_bounds__(256) void k_hist(BatchDev B, Group G, uint32_t post
   __syncthreads();
   for (uint32_t i = threadIdx.x; i < P.n_levels; i += blockDim.x)
     if (h[i]) atomicAdd(&P.hist[i], h[i]);
+}
+
+__global__ __launch_bounds__(256) void k_hist(BatchDev B, Group G, uint32_t post) {
+  const Member m = member_of(G);
+  hist_body(B.pops[m.pop], step_of(B, m.pop), m.lb, post);
 }
 
 // Position of this thread's element among the flagged elements of the block,
@@ -1386,91 +1390,21 @@ __global__ __launch_bounds__(kBlockCounts) void k_counts_inline(BatchDev B, Grou
   counts_body<true>(B, G, &t);
 }
 
-// Exclusive scan of the per-block sums (one workgroup per population), the
-// new population size R~' = sum n_i, and the capacity check.
-__global__ __launch_bounds__(1024) void k_scan(BatchDev B, Group G) {
-  __shared__ uint32_t scratch[1024 / kWave];
-  __shared__ unsigned long long cull_scratch[1024 / kWave];
-  const Member m = member_of(G);
-  const DevPop P = B.pops[m.pop];
-  if (P.sc->dead) return;
-  const PopStep sp = step_of(B, m.pop);
-  const uint32_t nb = P.n_blocks;
-  const uint32_t per = (nb + 1023) / 1024;
-  const uint32_t b0 = threadIdx.x * per;
-  uint32_t local = 0, cull = 0;
-  for (uint32_t b = b0; b < min(b0 + per, nb); ++b) {
-    local += P.block_sums[b];
-    cull += P.block_culled[b];
-  }
-  uint32_t total;
-  uint32_t run = block_exclusive_scan<1024>(local, &total, scratch);
-  for (uint32_t b = b0; b < min(b0 + per, nb); ++b) {
-    P.block_offsets[b] = run;
-    run += P.block_sums[b];
-  }
-  const unsigned long long ctot =
-      block_sum<1024, unsigned long long>((unsigned long long)cull, cull_scratch);
-  if (sp.flags & kStepHist) {  // for the histogram and family sums after the sweep
-    for (uint32_t j = threadIdx.x; j < P.n_levels; j += 1024) P.hist[j] = 0;
-    if (threadIdx.x == 0) P.sc->sum_eta2 = 0;
-  }
-  if (threadIdx.x == 0) {
-    const bool over = total > P.cap_limit;
-    P.sc->R_next = total;
-    P.sc->err = over ? 1u : 0u;
-    P.sc->n_culled = (uint32_t)ctot;
-    StepRecord* rec = record_of(B, m.pop);
-    if (rec) {
-      rec->n_culled = (uint32_t)ctot;
-      rec->status = over ? 1u : 0u;
-    }
-    if (over && (sp.flags & kStepSticky)) P.sc->dead = 1u;
-  }
-}
-
-// Offsets and the new-slot -> old-slot map of the order-preserving copy:
-// the n_i copies of old slot i take new slots offset_i .. offset_i + n_i - 1.
-// The block's new slots are written by all its threads together, slot j of
-// the block's range by thread j mod kBlockCounts: its source is the last old
-// slot t of the block whose exclusive offset is <= j (that slot has n_t > 0),
-// found by bisection over the offsets in LDS.  A step that gives one replica
-// many copies therefore costs no more than one that spreads them.
-__global__ __launch_bounds__(kBlockCounts) void k_scatter(BatchDev B, Group G) {
-  __shared__ uint32_t scratch[kBlockCounts / kWave];
-  __shared__ uint32_t excl_s[kBlockCounts];
-  const Member m = member_of(G);
-  const DevPop P = B.pops[m.pop];
-  if (P.sc->dead || P.sc->err) return;
-  const uint32_t R = P.sc->R_tilde;
-  const uint32_t i = m.lb * kBlockCounts + threadIdx.x;
-  const uint32_t n = i < R ? P.counts[i] : 0u;
-  uint32_t total;
-  const uint32_t excl = block_exclusive_scan<kBlockCounts>(n, &total, scratch);
-  const uint32_t base = P.block_offsets[m.lb];
-  if (i < R) P.offsets[i] = base + excl;
-  excl_s[threadIdx.x] = excl;
-  __syncthreads();
-  for (uint32_t j = threadIdx.x; j < total; j += kBlockCounts) {
-    uint32_t lo = 0, hi = kBlockCounts;  // excl_s[lo] <= j < excl_s[hi] (excl_s[kBlockCounts] = total)
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (excl_s[mid] <= j)
-        lo = mid;
-      else
-        hi = mid;
-    }
-    P.src[base + j] = m.lb * kBlockCounts + lo;
-  }
-}
-
-// The scan and the copy map of one population in one launch (calls on single
-// instances): workgroup b starts its new slots at the sum of the block sums
-// before it, then maps them as k_scatter does.  The last workgroup, whose
-// range ends at the new size R~', records it with the capacity check and the
-// culled count, and (kStepHist) clears the histogram and the family sum, as
-// k_scan does.  A workgroup whose range would pass the capacity writes
-// nothing; the overflow flag then keeps the sweep from applying the step.
+// The exclusive scan of the copy counts, the new population size R~' = sum n_i
+// with the capacity check, and the new-slot -> old-slot map of the
+// order-preserving copy: the n_i copies of old slot i take new slots offset_i ..
+// offset_i + n_i - 1.  Workgroup b starts its new slots at the sum of the block
+// sums before it.  The block's new slots are written by all its threads together,
+// slot j of the block's range by thread j mod kBlockCounts: its source is the last
+// old slot t of the block whose exclusive offset is <= j (that slot has n_t > 0),
+// found by bisection over the offsets in LDS, so a step that gives one replica
+// many copies costs no more than one that spreads them.  The last workgroup, whose
+// range ends at R~', records it with the capacity check and the culled count, and
+// (kStepHist) clears the histogram and the family sum.  A workgroup whose range
+// would pass the capacity writes nothing; the overflow flag then keeps the sweep
+// from applying the step.  (One launch for the sets of batches and steppers too,
+// whose scan of one workgroup per population and copy map were launches of their
+// own: 8.7 -> 4.9 us a step for eight populations.)
 __global__ __launch_bounds__(kBlockCounts) void k_scan_scatter(BatchDev B, Group G) {
   __shared__ uint32_t scratch[kBlockCounts / kWave];
   __shared__ uint32_t excl_s[kBlockCounts];
@@ -1531,10 +1465,19 @@ __global__ __launch_bounds__(kBlockCounts) void k_scan_scatter(BatchDev B, Group
   }
   if (threadIdx.x == 0) {
     const uint32_t all = base + total;
+    const bool over = all > P.cap_limit;
     P.sc->R_next = all;
-    P.sc->err = all > P.cap_limit ? 1u : 0u;
+    P.sc->err = over ? 1u : 0u;
     P.sc->n_culled = cull;
     if (sp.flags & kStepHist) P.sc->sum_eta2 = 0;
+    StepRecord* rec = record_of(B, m.pop);
+    if (rec) {
+      rec->n_culled = cull;
+      rec->status = over ? 1u : 0u;
+    }
+    // (a workgroup that starts after this leaves at once: nothing it would write
+    // is used)
+    if (over && (sp.flags & kStepSticky)) P.sc->dead = 1u;
   }
 }
 
@@ -1732,19 +1675,14 @@ __global__ __launch_bounds__(64) void k_energy(BatchDev B, Group G) {
 // the first kFamilyBlocks workgroups of a population work (the rest leave at
 // once), each over a stride of the slots, so that few atomic adds reach the
 // population's counter.
-constexpr uint32_t kFamilyBlocks = 512;
-
-__global__ __launch_bounds__(256) void k_family(BatchDev B, Group G, uint32_t post) {
+__device__ __forceinline__ void family_body(const DevPop& P, const PopStep& sp, uint32_t lb,
+                                            uint32_t blocks, uint32_t post) {
   __shared__ unsigned long long scratch[256 / kWave];
-  const Member m = member_of(G);
-  if (m.lb >= kFamilyBlocks) return;
-  const DevPop P = B.pops[m.pop];
   if (P.sc->dead) return;
-  const PopStep sp = step_of(B, m.pop);
   const uint32_t* fam = pick(P.fam, post ? sp.cur ^ 1u : sp.cur);
   const uint64_t R = P.sc->R_tilde;
   unsigned long long sq = 0;
-  for (uint64_t i = (uint64_t)m.lb * 256 + threadIdx.x; i < R; i += (uint64_t)kFamilyBlocks * 256) {
+  for (uint64_t i = (uint64_t)lb * 256 + threadIdx.x; i < R; i += (uint64_t)blocks * 256) {
     const uint32_t f = fam[i];
     if (i > 0 && fam[i - 1] == f) continue;
     // [i, in) lies in the run; the run ends at or before `out`
@@ -1765,6 +1703,25 @@ __global__ __launch_bounds__(256) void k_family(BatchDev B, Group G, uint32_t po
   }
   const unsigned long long s = block_sum<256, unsigned long long>(sq, scratch);
   if (threadIdx.x == 0 && s) atomicAdd(&P.sc->sum_eta2, s);
+}
+
+__global__ __launch_bounds__(256) void k_family(BatchDev B, Group G, uint32_t post) {
+  const Member m = member_of(G);
+  if (m.lb >= kFamilyBlocks) return;
+  family_body(B.pops[m.pop], step_of(B, m.pop), m.lb, kFamilyBlocks, post);
+}
+
+// Histogram and family sum of a set after its sweeps in one launch: the first
+// blocks_hist workgroups of a population count its energies, the others its
+// families (two launches took 6.5 + 8.5 us for eight populations).
+__global__ __launch_bounds__(256) void k_hist_family(BatchDev B, Group G) {
+  const Member m = member_of(G);
+  const DevPop& P = B.pops[m.pop];
+  const uint32_t nh = (P.capacity + kHistSlots - 1) / kHistSlots;
+  if (m.lb < nh)
+    hist_body(P, step_of(B, m.pop), m.lb, 1u);
+  else
+    family_body(P, step_of(B, m.pop), m.lb - nh, m.nb - nh, 1u);
 }
 
 // Post-step record of a batch step: integer sum of E over the population, the
@@ -2363,21 +2320,9 @@ hipError_t launch_counts_inline(const BatchDev& B, const Group& g, const InlineT
   return hipGetLastError();
 }
 
-hipError_t launch_scan(const BatchDev& B, const Group& g, hipStream_t stream) {
-  if (!g.blocks) return hipSuccess;
-  hipLaunchKernelGGL(k_scan, dim3(g.blocks), dim3(1024), 0, stream, B, g);
-  return hipGetLastError();
-}
-
 hipError_t launch_scan_scatter(const BatchDev& B, const Group& g, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
   hipLaunchKernelGGL(k_scan_scatter, dim3(g.blocks), dim3(kBlockCounts), 0, stream, B, g);
-  return hipGetLastError();
-}
-
-hipError_t launch_scatter(const BatchDev& B, const Group& g, hipStream_t stream) {
-  if (!g.blocks) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter, dim3(g.blocks), dim3(kBlockCounts), 0, stream, B, g);
   return hipGetLastError();
 }
 
@@ -2432,6 +2377,14 @@ hipError_t launch_energy(const BatchDev& B, const Group& g, uint32_t layout, uin
 }
 #undef PA_L_SWITCH
 #undef PA_L_SWITCH_S
+
+hipError_t launch_hist_family(const BatchDev& B, const Group& g, uint32_t max_levels,
+                              hipStream_t stream) {
+  if (!g.blocks) return hipSuccess;
+  hipLaunchKernelGGL(k_hist_family, dim3(g.blocks), dim3(256), (size_t)max_levels * 4, stream, B,
+                     g);
+  return hipGetLastError();
+}
 
 hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;

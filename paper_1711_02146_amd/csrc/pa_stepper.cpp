@@ -46,7 +46,7 @@ bool stepper_layout(uint32_t max_pops, uint32_t max_L, StepperLayout* out) {
   const size_t N = (size_t)max_L * max_L * max_L;
   // groups: per-pop, slots and histogram (n ids + n + 1 starts each), sweep
   // groups (n ids + one start per group + n; at most 14 (layout, L) kinds)
-  l.n_u32 = 3 * (2 * (size_t)max_pops + 1) + (2 * (size_t)max_pops + 16);
+  l.n_u32 = 4 * (2 * (size_t)max_pops + 1) + (2 * (size_t)max_pops + 16);
   l.e_doubles = (size_t)max_pops * (3 * N + 1);
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -172,20 +172,22 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
     ps.gather = 1;
     ps.cur = in->cur;
     ps.step = in->step + 1;
-    ps.flags = pa::kStepSticky;
+    ps.flags = pa::kStepSticky | pa::kStepHist;
     e_used += in->dev.n_levels;
   }
   pa_host::GroupTables gt;
   gt.d_base = reinterpret_cast<uint32_t*>(w + l.off_u32);
-  std::vector<uint32_t> all(n), one(n, 1), slots(n), hist(n);
+  std::vector<uint32_t> all(n), one(n, 1), slots(n), hist(n), post(n);
   for (uint32_t p = 0; p < n; ++p) {
     all[p] = p;
     slots[p] = pa::blocks_slots(pops[p]->dev.capacity);
     hist[p] = pa::blocks_hist(pops[p]->dev.capacity);
+    post[p] = pa::blocks_hist_family(pops[p]->dev.capacity);
   }
   const pa::Group g_perpop = gt.add(all, one);
   const pa::Group g_slots = gt.add(all, slots);
   const pa::Group g_hist = gt.add(all, hist);
+  const pa::Group g_post = gt.add(all, post);
   struct SweepGroup {
     uint32_t layout, L;
     uint32_t split;  // waves per tile
@@ -225,13 +227,10 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
             pa::launch_hist(B, g_hist, max_levels, false, st) == hipSuccess &&
             pa::launch_table(B, g_perpop, st) == hipSuccess &&
             pa::launch_counts(B, g_slots, st) == hipSuccess &&
-            pa::launch_scan(B, g_perpop, st) == hipSuccess &&
-            pa::launch_scatter(B, g_slots, st) == hipSuccess;
+            pa::launch_scan_scatter(B, g_slots, st) == hipSuccess;
   for (const auto& sg : g_sweep) ok = ok && pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, st) ==
                                              hipSuccess;
-  ok = ok && pa::launch_zero_acc(B, g_perpop, st) == hipSuccess &&
-       pa::launch_hist(B, g_hist, max_levels, true, st) == hipSuccess &&
-       pa::launch_family(B, g_slots, true, st) == hipSuccess &&
+  ok = ok && pa::launch_hist_family(B, g_post, max_levels, st) == hipSuccess &&
        pa::launch_record(B, g_perpop, st) == hipSuccess;
   if (!ok) return dev_fail();
   if (hipMemcpyAsync(s->h_rec, w + l.off_rec, (size_t)n * sizeof(pa::StepRecord),
