@@ -84,6 +84,7 @@ struct pa_batch {
   struct SweepGroup {
     uint32_t layout, L;
     uint32_t split;  // waves per tile
+    uint64_t work;   // sites x tiles
     pa::Group g;
   };
   std::vector<SweepGroup> g_sweep;
@@ -94,6 +95,7 @@ struct pa_batch {
   std::vector<PairGroup> g_pairs;  // one overlap launch per spin layout
   const uint32_t* d_pair_pops = nullptr;
   uint32_t max_levels = 0;
+  pa_host::SideStream side;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
   // starting point of every population
@@ -122,8 +124,10 @@ int capture_step(pa_batch* b) {
   bool ok = pa::launch_table(B, b->g_perpop, s) == hipSuccess &&
             pa::launch_counts(B, b->g_slots, s) == hipSuccess &&
             pa::launch_scan_scatter(B, b->g_slots, s) == hipSuccess;
-  for (const auto& sg : b->g_sweep)
-    ok = ok && pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, s) == hipSuccess;
+  const auto sweep = [&](const pa_batch::SweepGroup& sg, hipStream_t st) {
+    return pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, st);
+  };
+  ok = ok && pa_host::launch_sweeps(b->g_sweep, b->side, s, sweep) == hipSuccess;
   ok = ok && pa::launch_hist_family(B, b->g_post, b->max_levels, s) == hipSuccess &&
        pa::launch_record(B, b->g_perpop, s) == hipSuccess;
   for (const auto& pg : b->g_pairs)
@@ -267,7 +271,9 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
     const uint32_t per_block = pa::sweep_tiles(pa::kModelPm, kv.first.second, split);
     std::vector<uint32_t> nb;
     for (uint32_t p : kv.second) nb.push_back(pa::blocks_sweep(pops[p]->dev.capacity, per_block));
-    b->g_sweep.push_back({kv.first.first, kv.first.second, split, add_group(kv.second, nb)});
+    b->g_sweep.push_back({kv.first.first, kv.first.second, split,
+                          tiles * kv.first.second * kv.first.second * kv.first.second,
+                          add_group(kv.second, nb)});
   }
   for (uint32_t layout : {(uint32_t)PA_LAYOUT_INT8, (uint32_t)PA_LAYOUT_BITPACK64}) {
     std::vector<uint32_t> ids, nb;
@@ -325,6 +331,7 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
       pa::launch_hist(B, b->g_hist, b->max_levels, false, s) != hipSuccess)
     return fail(PA_EDEVICE);
   if (hipStreamSynchronize(s) != hipSuccess) return fail(PA_EDEVICE);
+  if (b->g_sweep.size() > 1) b->side.create();
   const int rc = capture_step(b);
   if (rc) return fail(rc);
   for (uint32_t p = 0; p < n_pops; ++p) pops[p]->in_batch = true;
@@ -431,6 +438,7 @@ int pa_batch_free(pa_batch* b) {
   if (b->stream) (void)hipStreamSynchronize(b->stream);
   if (b->exec) (void)hipGraphExecDestroy(b->exec);
   if (b->graph) (void)hipGraphDestroy(b->graph);
+  b->side.destroy();
   for (pa_instance* in : b->pops)
     if (in) in->in_batch = false;
   delete b;

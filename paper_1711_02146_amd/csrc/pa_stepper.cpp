@@ -74,6 +74,8 @@ struct pa_stepper {
   StepperLayout lay{};
   uint8_t* h_img = nullptr;         // pinned host image of the workspace prefix
   pa::StepRecord* h_rec = nullptr;  // pinned records
+  pa_host::SideStream side;         // made by the first step with more than one lattice size
+  bool side_made = false;
   bool failed = false;
 };
 
@@ -113,6 +115,7 @@ int pa_stepper_create(uint32_t max_pops, uint32_t max_L, void* d_workspace, size
 int pa_stepper_free(pa_stepper* s) {
   if (!s) return PA_EINVAL;
   if (s->stream) (void)hipStreamSynchronize(s->stream);
+  s->side.destroy();
   if (s->h_img) (void)hipHostFree(s->h_img);
   if (s->h_rec) (void)hipHostFree(s->h_rec);
   delete s;
@@ -191,6 +194,7 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
   struct SweepGroup {
     uint32_t layout, L;
     uint32_t split;  // waves per tile
+    uint64_t work;   // sites x tiles
     pa::Group g;
   };
   std::vector<SweepGroup> g_sweep;
@@ -204,7 +208,9 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
     const uint32_t per_block = pa::sweep_tiles(pa::kModelPm, kv.first.second, split);
     std::vector<uint32_t> nb;
     for (uint32_t p : kv.second) nb.push_back(pa::blocks_sweep(pops[p]->dev.capacity, per_block));
-    g_sweep.push_back({kv.first.first, kv.first.second, split, gt.add(kv.second, nb)});
+    g_sweep.push_back({kv.first.first, kv.first.second, split,
+                       tiles * kv.first.second * kv.first.second * kv.first.second,
+                       gt.add(kv.second, nb)});
   }
   if (gt.u32.size() > l.n_u32) return PA_EINVAL;
   std::memcpy(img + l.off_u32, gt.u32.data(), gt.u32.size() * 4);
@@ -228,8 +234,14 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
             pa::launch_table(B, g_perpop, st) == hipSuccess &&
             pa::launch_counts(B, g_slots, st) == hipSuccess &&
             pa::launch_scan_scatter(B, g_slots, st) == hipSuccess;
-  for (const auto& sg : g_sweep) ok = ok && pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, st) ==
-                                             hipSuccess;
+  if (g_sweep.size() > 1 && !s->side_made) {
+    s->side.create();
+    s->side_made = true;
+  }
+  const auto sweep = [&](const SweepGroup& sg, hipStream_t where) {
+    return pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, where);
+  };
+  ok = ok && pa_host::launch_sweeps(g_sweep, s->side, st, sweep) == hipSuccess;
   ok = ok && pa::launch_hist_family(B, g_post, max_levels, st) == hipSuccess &&
        pa::launch_record(B, g_perpop, st) == hipSuccess;
   if (!ok) return dev_fail();
