@@ -112,11 +112,12 @@ __host__ __device__ constexpr uint32_t pm_tiles(uint32_t L, uint32_t split) {
 // per workgroup, bytes of a wave's plane area (16 sites x 64 replicas, one byte
 // each), waves per SIMD that its registers are budgeted for (as many as the LDS
 // lets run, at most five), and the workgroups that fill 256 CUs.
-constexpr uint32_t kGaussLds = 2;
+constexpr uint32_t kGaussLds = 2;     // several tiles per workgroup
+constexpr uint32_t kGaussLdsOne = 3;  // one tile, for launches that leave the chip idle
 constexpr uint32_t kGaussPlaneBytes = 16 * 64;
 __host__ __device__ constexpr uint32_t gauss_waves(uint32_t L) { return L == 10 ? 16 : 8; }
-__host__ __device__ constexpr uint32_t gauss_tiles(uint32_t L) {
-  return L == 4 ? 8 : L == 6 ? 4 : 2;
+__host__ __device__ constexpr uint32_t gauss_tiles(uint32_t L, uint32_t form) {
+  return form == kGaussLdsOne ? 1 : L == 4 ? 8 : L == 6 ? 4 : 2;
 }
 constexpr int kGaussWavesPerEu = 4;
 inline uint32_t gauss_resident(uint32_t L) {
@@ -429,12 +430,14 @@ inline uint32_t blocks_sweep(uint32_t capacity, uint32_t per_block) {
 }
 // Tiles per workgroup of a sweep launch.
 inline uint32_t sweep_tiles(uint32_t model, uint32_t L, uint32_t split) {
-  return model == kModelPm ? pm_tiles(L, split) : split == kGaussLds ? gauss_tiles(L) : 1;
+  return model == kModelPm ? pm_tiles(L, split) : split == kGaussLds ? gauss_tiles(L, split) : 1;
 }
 // Workgroups of a sweep launch of one population.
 inline uint32_t sweep_blocks(uint32_t model, uint32_t L, uint32_t split, uint32_t capacity) {
   const uint32_t all = blocks_sweep(capacity, sweep_tiles(model, L, split));
-  return model != kModelPm && split == kGaussLds ? std::min(all, gauss_resident(L)) : all;
+  return model != kModelPm && (split == kGaussLds || split == kGaussLdsOne)
+             ? std::min(all, gauss_resident(L))
+             : all;
 }
 // Waves per workgroup of a sweep launch over `tiles` tiles of linear size L, from
 // timings on MI355X (10 sweeps, beta = 1).
@@ -445,24 +448,26 @@ inline uint32_t sweep_blocks(uint32_t model, uint32_t L, uint32_t split, uint32_
 // waves still have a full chunk each (L = 12, 3125 tiles 1.152 / 1.175; L = 16,
 // 1563 tiles 1.52 / 1.92); at L = 6 four are never slower (157 tiles 0.046 /
 // 0.046, 1563 tiles 0.186 / 0.132).
-// Gaussian models, L <= 10: four (the form with its table in LDS, which fills a
-// CU with one or two workgroups of several tiles) once the launch fills the chip
-// that way, the eight-wave kernel below (ms per launch of 10 sweeps, table in LDS /
-// eight waves, real couplings: L = 4, 512 tiles 0.054 / 0.049, 768 tiles 0.055 /
-// 0.066; L = 6, 512 tiles 0.100 / 0.082, 768 tiles 0.101 / 0.108; L = 8, 256 tiles
-// 0.113 / 0.083, 512 tiles 0.118 / 0.139; L = 10, 256 tiles 0.152 / 0.133, 384
-// tiles 0.156 / 0.221, 7813 tiles 2.27 / 3.03).  From L = 12 up, where the table
-// does not fit, eight.
+// Gaussian models, L <= 10: several tiles per workgroup (4) once that fills the
+// chip, one (8) below (ms per launch of 10 sweeps with several / one, real
+// couplings: L = 4, 768 tiles 0.055 / 0.046, 1024 tiles 0.054 / 0.062; L = 6, 313
+// tiles 0.098 / 0.055, 1024 tiles 0.102 / 0.102, 1536 tiles 0.134 / 0.148; L = 8,
+// 1024 tiles 0.165 / 0.176, 1536 tiles 0.266 / 0.256, 2048 tiles 0.327 / 0.351).  At
+// L = 10 a workgroup fills a CU either way, a round of 256 workgroups takes 5 parts
+// of time with two tiles each against 3 with one (512 tiles 0.152 / 0.168, 768
+// tiles 0.293 / 0.256, 1024 tiles 0.292 / 0.327, 7813 tiles 2.27 / 2.45), and the
+// rounds decide.  From L = 12 up (k_sweep: the table does not fit) eight waves.
 inline uint32_t sweep_split_default(uint32_t model, uint32_t L, uint64_t tiles) {
   if (model == kModelPm) {
     const uint64_t few = L == 4 ? 512 : L == 6 ? 0 : L == 8 ? 256 : 768;
     return L >= 12 || tiles < few ? 8u : 4u;
   }
-  const uint64_t few = L <= 6 ? 640 : L == 8 ? 384 : 320;
+  if (L == 10) return 5 * ((tiles + 511) / 512) < 3 * ((tiles + 255) / 256) ? 4u : 8u;
+  const uint64_t few = L == 4 ? 900 : L == 6 ? 1100 : 1600;
   return L >= 12 || tiles < few ? 8u : 4u;
 }
-// The kernel form of a launch with `split` waves per workgroup.  Gaussian models on
-// four waves, L <= 10: the kernel with its table in LDS.  +-J on four waves
+// The kernel form of a choice of 4 or 8.  Gaussian models, L <= 10: the kernel with
+// its table in LDS, on several tiles or one.  Otherwise waves per workgroup; +-J on four waves
 // packs several tiles per workgroup where there are enough of them (ms per
 // launch packed / one tile per workgroup: L = 4, 313 tiles 0.044 / 0.047, 7813
 // tiles 0.157 / 0.333; L = 6, 782 tiles 0.104 / 0.086, 1563 tiles 0.128 / 0.132,
@@ -470,7 +475,7 @@ inline uint32_t sweep_split_default(uint32_t model, uint32_t L, uint64_t tiles) 
 // 0.382, 7813 tiles 0.824 / 0.873).
 inline uint32_t sweep_form(uint32_t model, uint32_t L, uint32_t split, uint64_t tiles) {
   const uint64_t enough = L == 4 ? 0 : L == 6 ? 1500 : 3200;
-  if (model != kModelPm) return split == 4 && L <= 10 ? kGaussLds : split;
+  if (model != kModelPm) return L > 10 ? split : split == 4 ? kGaussLds : kGaussLdsOne;
   return split == 4 && L <= 8 && tiles >= enough ? kPmPacked : split;
 }
 // The form a launch uses: sweep_form of the autotuner's choice for (model,

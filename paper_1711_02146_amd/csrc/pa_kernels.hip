@@ -1493,13 +1493,13 @@ __global__ __launch_bounds__(kBlockCounts) void k_scan_scatter(BatchDev B, Group
 // of each tile by the same factor.
 //
 // Register budget: as many waves per SIMD as fit without spilling to scratch
-// memory (seven up to L = 8, six at 10, five at 12 and 14, four at 16).  (+-J
-// populations: k_sweep_pm.  Gaussian ones up to L = 10 that fill the chip:
-// k_sweep_gauss; this kernel then takes the smaller launches, on eight waves.)
+// memory (five at L = 12 and 14, four at 16).  (Gaussian models from L = 12 up.
+// Below, the threshold table fits in LDS: k_sweep_gauss; +-J: k_sweep_pm.)
 template <int L, int M>
 constexpr int sweep_min_waves_per_eu() {
   static_assert(M == (int)kModelGauss16 || M == (int)kModelReal, "Gaussian models");
-  return L <= 8 ? 7 : L == 10 ? 6 : L <= 14 ? 5 : 4;
+  static_assert(L >= 12, "smaller lattices: k_sweep_gauss");
+  return L <= 14 ? 5 : 4;
 }
 
 template <int LAYOUT, int L, int SPLIT, int M>
@@ -2123,40 +2123,7 @@ __global__ __launch_bounds__(256) void k_import_spins(void* spins, const uint16_
 template <int LAYOUT, int L>
 void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t model,
                     hipStream_t stream) {
-  // k_sweep, after the tile image: the plane areas (one per wave; the reduction
-  // area lies over them) and the quantised threshold table
-  const size_t after = model == kModelGauss16
-                           ? (size_t)kPlaneAreaBytes * split + (size_t)(kGaussDEMax + 1) * 8
-                           : (size_t)kPlaneAreaBytes * split;
-  static_assert(kPlaneAreaBytes >= 8 * 64, "the reduction area lies over the plane areas");
-  const size_t lds = (size_t)L * L * L * 8 + after;
-  if constexpr (L <= 10) {
-    if (model != kModelPm && split == kGaussLds) {
-      const dim3 grid(g.blocks), block(64 * gauss_waves(L));
-      if (model == kModelReal)
-        hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelReal>), grid, block,
-                           GaussShape<L>::bytes, stream, B, g);
-      else
-        hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelGauss16>), grid, block,
-                           GaussShape<L>::bytes, stream, B, g);
-      return;
-    }
-  }
-  if (model == kModelReal) {
-    if (split == 8 || L <= 10)
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelReal>), dim3(g.blocks), dim3(64 * 8), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, L <= 10 ? 8 : 4, kModelReal>), dim3(g.blocks), dim3(64 * 4), lds,
-                         stream, B, g);
-  } else if (model == kModelGauss16) {
-    if (split == 8 || L <= 10)
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelGauss16>), dim3(g.blocks), dim3(64 * 8), lds,
-                         stream, B, g);
-    else
-      hipLaunchKernelGGL((k_sweep<LAYOUT, L, L <= 10 ? 8 : 4, kModelGauss16>), dim3(g.blocks), dim3(64 * 4), lds,
-                         stream, B, g);
-  } else {
+  if (model == kModelPm) {
     const size_t lds_pm = kPmImage + (size_t)L * L * L * 8 * pm_tiles(L, split) +
                           kPmPlaneBytes * pm_waves(split);
     const dim3 grid(g.blocks), block(64 * pm_waves(split));
@@ -2167,6 +2134,36 @@ void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t 
                          stream, B, g);
     else
       hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, 4>), grid, block, lds_pm, stream, B, g);
+  } else if constexpr (L <= 10) {
+    constexpr size_t lds = GaussShape<L, kGaussLds>::bytes, lds1 = GaussShape<L, kGaussLdsOne>::bytes;
+    const dim3 grid(g.blocks), block(64 * gauss_waves(L));
+    if (model == kModelReal && split == kGaussLds)
+      hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelReal, kGaussLds>), grid, block, lds,
+                         stream, B, g);
+    else if (model == kModelReal)
+      hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelReal, kGaussLdsOne>), grid, block, lds1,
+                         stream, B, g);
+    else if (split == kGaussLds)
+      hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelGauss16, kGaussLds>), grid, block, lds,
+                         stream, B, g);
+    else
+      hipLaunchKernelGGL((k_sweep_gauss<LAYOUT, L, kModelGauss16, kGaussLdsOne>), grid, block, lds1,
+                         stream, B, g);
+  } else {
+    // after the tile image: the plane areas (one per wave; the reduction area lies
+    // over them) and the quantised threshold table
+    static_assert(kPlaneAreaBytes >= 8 * 64, "the reduction area lies over the plane areas");
+    const size_t lds = (size_t)L * L * L * 8 + (size_t)kPlaneAreaBytes * split +
+                       (model == kModelGauss16 ? (size_t)(kGaussDEMax + 1) * 8 : 0);
+    const dim3 grid(g.blocks), block(64 * split);
+    if (model == kModelReal && split == 8)
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelReal>), grid, block, lds, stream, B, g);
+    else if (model == kModelReal)
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelReal>), grid, block, lds, stream, B, g);
+    else if (split == 8)
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 8, kModelGauss16>), grid, block, lds, stream, B, g);
+    else
+      hipLaunchKernelGGL((k_sweep<LAYOUT, L, 4, kModelGauss16>), grid, block, lds, stream, B, g);
   }
 }
 
@@ -2354,9 +2351,10 @@ hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint
                         uint32_t split, uint32_t model, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
   if (split != 4 && split != 8 && !(split == kPmPacked && model == kModelPm && L <= 8) &&
-      !(split == kGaussLds && model != kModelPm && L <= 10 && g.n == 1))
+      !((split == kGaussLds || split == kGaussLdsOne) && model != kModelPm && L <= 10 &&
+        g.n == 1))
     return hipErrorInvalidValue;
-  if (split == 4 && model != kModelPm && L <= 10) return hipErrorInvalidValue;
+  if (split >= 4 && model != kModelPm && L <= 10) return hipErrorInvalidValue;
   if (layout == 2) {
     PA_L_SWITCH_S(launch_sweep_l, 2)
   } else {

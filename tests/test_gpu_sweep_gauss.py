@@ -1,6 +1,6 @@
-"""The Gaussian sweep kernel with its threshold table in LDS (L <= 10, four-wave
-choice) and the eight-wave kernel beside it against the oracle: part-filled last
-tiles and workgroups, more tiles than the resident workgroups take at once,
+"""The Gaussian sweep kernel with its threshold table in LDS (L <= 10), on several
+tiles per workgroup (split 4) and on one (split 8, where a wave may have no sites),
+against the oracle: part-filled last tiles and workgroups, more tiles than the resident workgroups take at once,
 inverse temperatures at which every threshold is 2^32, shares its upper half with
 most others, or is 0 (the draws that only the exact threshold decides: one in
 2^16), and a copy step whose sources lie in one, several and many old tiles.
@@ -55,12 +55,13 @@ def test_forms_and_thresholds(pam, model, L, split, beta):
     g.close()
 
 
-# tiles past the 256 * 16 / W workgroups of T tiles that are resident at once, and
-# sizes on either side of the default rule
+# tiles past those that the resident workgroups take at once, and sizes on either
+# side of the default rule
 @pytest.mark.parametrize("model", ["gauss16", "gauss"])
 @pytest.mark.parametrize("layout", ["int8", "bitpack64"])
-@pytest.mark.parametrize("L,R", [(4, 64 * 639 + 1), (4, 64 * 4097 + 1), (6, 64 * 640), (6, 64 * 2049),
-                                 (8, 64 * 1027 + 63), (10, 64 * 319 + 5), (10, 64 * 513 + 1)])
+@pytest.mark.parametrize("L,R", [(4, 64 * 899), (4, 64 * 4097 + 1), (6, 64 * 1098 + 1), (6, 64 * 2049),
+                                 (8, 64 * 1027 + 63), (8, 64 * 1600), (10, 64 * 256),
+                                 (10, 64 * 257 + 5), (10, 64 * 513 + 1), (10, 64 * 770)])
 def test_sizes(pam, model, layout, L, R):
     pam.pa_autotune_reset()
     g, o = pair(pam, model, L, R, 77 + L, layout)
