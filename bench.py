@@ -36,7 +36,7 @@ GAUSS_WORKLOAD = dict(name="L10_R500k_bitpack64_gauss16_adaptive_eps0.1", L=10, 
                       eps=0.1, beta_max=5.0, n_sweeps=10, layout="bitpack64", model="gauss16")
 
 # The same anneal with the couplings as real numbers (unit normals on the grid
-# 2^-32): per-replica weights, exact fixed-point sums, the bisection on the device.
+# 2^-32): per-replica weights, exact fixed-point sums, the step search on the device.
 REAL_WORKLOAD = dict(name="L10_R500k_bitpack64_gauss_real_adaptive_eps0.1", L=10, R=500000,
                      eps=0.1, beta_max=5.0, n_sweeps=10, layout="bitpack64", model="gauss")
 
@@ -89,16 +89,16 @@ BYTES_PER_REPLICA_FIXED = 20
 # lane-instructions per attempt = SQ_INSTS_VALU x 64 / attempts per launch.
 # None: no counters for the current source yet.
 PROFILE = {
-    "kernel_src_sha256": "09a636d0398f288f2ffcc9e73ed17ebb9a9070905e5d048eb50c82aaedef6373",
+    "kernel_src_sha256": "cafc116031d74c0047471f25c6fce24502fc551232b38f298521264a061824e5",
     # FETCH_SIZE KiB x 2 + WRITE_SIZE KiB x 1, per launch (profiles/*_hbm_counters.md)
-    "bytes_per_launch": (32861.6 * 2 + 64946.1) * 1024,
-    "gauss16_bytes_per_launch": (33336.6 * 2 + 64942.5) * 1024,
-    "real_bytes_per_launch": (35163.6 * 2 + 66898.5) * 1024,
-    "link_overlap_bytes_per_launch": (61563.2 * 2 + 10484.4) * 1024,
-    "int8_C2_bytes_per_launch": (26059.5 * 2 + 50797.2) * 1024,
-    "int8_overlap_bytes_per_call": (50034.2 * 2 + 342.9) * 1024,
-    # SQ_INSTS_VALU 1.0286e9 per launch x 64 lanes / 5.0e9 attempts
-    "valu_per_attempt": 1.0286e9 * 64 / 5.0e9,
+    "bytes_per_launch": (32873.3 * 2 + 64946.1) * 1024,
+    "gauss16_bytes_per_launch": (33243.9 * 2 + 64942.5) * 1024,
+    "real_bytes_per_launch": (37814.7 * 2 + 66898.5) * 1024,
+    "link_overlap_bytes_per_launch": (63921.8 * 2 + 10484.4) * 1024,
+    "int8_C2_bytes_per_launch": (25947.7 * 2 + 50797.2) * 1024,
+    "int8_overlap_bytes_per_call": (50037.0 * 2 + 51.9) * 1024,
+    # SQ_INSTS_VALU 1.0344e9 per launch x 64 lanes / 5.0e9 attempts
+    "valu_per_attempt": 1.0344e9 * 64 / 5.0e9,
 }
 
 

@@ -1404,7 +1404,7 @@ __global__ __launch_bounds__(kBlockCounts) void k_counts_inline(BatchDev B, Grou
 // would pass the capacity writes nothing; the overflow flag then keeps the sweep
 // from applying the step.  (One launch for the sets of batches and steppers too,
 // whose scan of one workgroup per population and copy map were launches of their
-// own: 8.7 -> 4.9 us a step for eight populations.)
+// own: 8.7 -> 5.5 us a step for up to eight populations, 18.4 -> 16.8 for 24.)
 __global__ __launch_bounds__(kBlockCounts) void k_scan_scatter(BatchDev B, Group G) {
   __shared__ uint32_t scratch[kBlockCounts / kWave];
   __shared__ uint32_t excl_s[kBlockCounts];
@@ -1713,7 +1713,8 @@ __global__ __launch_bounds__(256) void k_family(BatchDev B, Group G, uint32_t po
 
 // Histogram and family sum of a set after its sweeps in one launch: the first
 // blocks_hist workgroups of a population count its energies, the others its
-// families (two launches took 6.5 + 8.5 us for eight populations).
+// families (for up to eight populations 6.5 + 8.5 us in two launches, 10.8 in one;
+// for 24 populations 9.7 + 22.3 and 30.3).
 __global__ __launch_bounds__(256) void k_hist_family(BatchDev B, Group G) {
   const Member m = member_of(G);
   const DevPop& P = B.pops[m.pop];
