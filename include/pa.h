@@ -151,7 +151,8 @@ size_t pa_workspace_bytes(const pa_params* p);
  * J_host: 3*L^3 couplings, +1/-1 (PA_MODEL_PM) or k in [-127, 127]
  * (PA_MODEL_GAUSS16), copied; any other value is PA_EINVAL.  d_workspace: device memory of at
  * least pa_workspace_bytes(p) bytes, owned by the caller.  hip_stream: the
- * hipStream_t all work of this instance is queued on (NULL = default stream).
+ * hipStream_t all work of this instance is queued on (NULL = default stream; in a
+ * batch or stepper of several lattice sizes see pa_batch_create, pa_stepper_create).
  * On success *out holds the new instance. */
 int pa_init_instance(const pa_params* p, const int8_t* J_host, void* d_workspace, size_t ws_bytes,
                      void* hip_stream, pa_instance** out);
@@ -353,7 +354,10 @@ size_t pa_batch_workspace_bytes(uint32_t n_pops, uint32_t n_pairs, uint32_t n_st
  * pairs: 2 * n_pairs instance indices (same L and layout within a pair) whose
  * overlap histogram (pa_overlap_hist's binning) is recorded after every step;
  * may be NULL when n_pairs = 0.  The caller owns d_workspace
- * (pa_batch_workspace_bytes bytes) until pa_batch_free.  Synchronises. */
+ * (pa_batch_workspace_bytes bytes) until pa_batch_free.  A batch of several lattice
+ * sizes runs part of its sweeps on a stream of its own, made here on the device of
+ * the instances' stream (default priority, all compute units) and ordered within the
+ * steps on that stream by events.  Synchronises. */
 int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* pairs,
                     uint32_t n_pairs, const double* betas, uint32_t n_steps, uint32_t n_sweeps,
                     void* d_workspace, size_t ws_bytes, pa_batch** out);
@@ -390,7 +394,10 @@ typedef struct pa_stepper pa_stepper;
 size_t pa_stepper_workspace_bytes(uint32_t max_pops, uint32_t max_L);
 
 /* Create a stepper that launches on hip_stream (every instance it steps must
- * have been created on that stream).  The caller owns d_workspace
+ * have been created on that stream).  A stepper of several instances also makes a
+ * stream of its own on the same device (default priority, all compute units): a step
+ * over several lattice sizes runs part of its sweeps there, ordered within the step
+ * on hip_stream by events.  The caller owns d_workspace
  * (pa_stepper_workspace_bytes bytes, 256-byte aligned) until pa_stepper_free.
  * libpa allocates a pinned host staging image of the same size. */
 int pa_stepper_create(uint32_t max_pops, uint32_t max_L, void* d_workspace, size_t ws_bytes,

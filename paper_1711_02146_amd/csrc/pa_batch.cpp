@@ -331,7 +331,7 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
       pa::launch_hist(B, b->g_hist, b->max_levels, false, s) != hipSuccess)
     return fail(PA_EDEVICE);
   if (hipStreamSynchronize(s) != hipSuccess) return fail(PA_EDEVICE);
-  if (b->g_sweep.size() > 1) b->side.create();
+  if (b->g_sweep.size() > 1) b->side.create(s);
   const int rc = capture_step(b);
   if (rc) return fail(rc);
   for (uint32_t p = 0; p < n_pops; ++p) pops[p]->in_batch = true;

@@ -4,13 +4,13 @@
 
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <cmath>
 #include <cstdint>
 #include <vector>
 
 #include "../../include/pa.h"
 #include "pa_internal.hpp"
+#include "pa_side_stream.hpp"
 
 namespace pa_host {
 
@@ -62,63 +62,6 @@ struct GroupTables {
     return g;
   }
 };
-
-// A second stream beside a set's own, for the sweep launches of its lattice sizes
-// (one launch each): alone, the last workgroups of a launch leave most of the chip
-// idle until they end (a loop of eight requests 229 -> 222 ms, a batch of 12 pairs
-// 341 -> 334).  Without it (creation failed) the launches follow each other.
-struct SideStream {
-  hipStream_t s = nullptr;
-  hipEvent_t fork = nullptr, join = nullptr;
-
-  void create() {
-    if (hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess) s = nullptr;
-    if (!s || hipEventCreateWithFlags(&fork, hipEventDisableTiming) != hipSuccess ||
-        hipEventCreateWithFlags(&join, hipEventDisableTiming) != hipSuccess) {
-      destroy();
-      (void)hipGetLastError();  // not an error of the launches that follow
-    }
-  }
-  void destroy() {
-    if (fork) (void)hipEventDestroy(fork);
-    if (join) (void)hipEventDestroy(join);
-    if (s) (void)hipStreamDestroy(s);
-    s = nullptr;
-    fork = join = nullptr;
-  }
-};
-
-// The launches of a set's sweep groups (launch(group, stream)) on `stream` and the
-// side stream, the largest first, each on the one with less work so far; what
-// follows on `stream` waits for both.
-template <typename SweepGroup, typename Launch>
-hipError_t launch_sweeps(const std::vector<SweepGroup>& groups, const SideStream& side,
-                         hipStream_t stream, Launch launch) {
-  const bool two = side.s && groups.size() > 1;
-  hipError_t e = hipSuccess;
-  if (two) {
-    e = hipEventRecord(side.fork, stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(side.s, side.fork, 0);
-    if (e != hipSuccess) return e;
-  }
-  std::vector<const SweepGroup*> order;
-  for (const SweepGroup& g : groups) order.push_back(&g);
-  std::sort(order.begin(), order.end(),
-            [](const SweepGroup* a, const SweepGroup* b) { return a->work > b->work; });
-  uint64_t mine = 0, other = 0;
-  for (const SweepGroup* g : order) {
-    const bool here = !two || mine <= other;
-    (here ? mine : other) += g->work;
-    const hipError_t l = launch(*g, here ? stream : side.s);
-    if (e == hipSuccess) e = l;
-  }
-  if (two) {
-    const hipError_t r = hipEventRecord(side.join, side.s);
-    const hipError_t w = r == hipSuccess ? hipStreamWaitEvent(stream, side.join, 0) : r;
-    if (e == hipSuccess) e = w;
-  }
-  return e;
-}
 
 // Metropolis thresholds: accept dE > 0 iff word < floor(2^32 exp(-beta dE)).
 inline void thresholds(double beta, unsigned long long thr[3]) {

@@ -74,8 +74,7 @@ struct pa_stepper {
   StepperLayout lay{};
   uint8_t* h_img = nullptr;         // pinned host image of the workspace prefix
   pa::StepRecord* h_rec = nullptr;  // pinned records
-  pa_host::SideStream side;         // made by the first step with more than one lattice size
-  bool side_made = false;
+  pa_host::SideStream side;         // for steps with more than one lattice size
   bool failed = false;
 };
 
@@ -108,6 +107,7 @@ int pa_stepper_create(uint32_t max_pops, uint32_t max_L, void* d_workspace, size
     pa_stepper_free(s);
     return PA_EDEVICE;
   }
+  if (max_pops > 1) s->side.create(s->stream);
   *out = s;
   return PA_OK;
 }
@@ -234,10 +234,6 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
             pa::launch_table(B, g_perpop, st) == hipSuccess &&
             pa::launch_counts(B, g_slots, st) == hipSuccess &&
             pa::launch_scan_scatter(B, g_slots, st) == hipSuccess;
-  if (g_sweep.size() > 1 && !s->side_made) {
-    s->side.create();
-    s->side_made = true;
-  }
   const auto sweep = [&](const SweepGroup& sg, hipStream_t where) {
     return pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, where);
   };
