@@ -368,6 +368,25 @@ void resolve_scratch(int dev) {
     g_scratch_ptr[dev] = static_cast<uint32_t*>(p);
 }
 
+// The kernels' code onto the device of the stream, at the first instance created
+// there: once loaded it stays for the process.  A failure shows at the launch that
+// needs the code.
+std::atomic<uint64_t> g_code_loaded{0};  // bit d: device d
+
+void load_code_beside(hipStream_t stream) {
+  int dev = -1;
+  if (hipStreamGetDevice(stream, &dev) == hipSuccess && dev >= 0 && dev < kMaxDevices &&
+      ((g_code_loaded.load(std::memory_order_relaxed) >> dev) & 1u))
+    return;
+  const pa_host::DeviceOf current(stream);
+  if (!current.ok() || pa::load_code() != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (dev >= 0 && dev < kMaxDevices)
+    g_code_loaded.fetch_or(1ull << dev, std::memory_order_relaxed);
+}
+
 uint32_t* scratch_of(int dev) {
   if (dev < 0 || dev >= kMaxDevices) return nullptr;
   std::lock_guard<std::mutex> lock(g_scratch_mu);
@@ -1182,6 +1201,7 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
   }
   resolve_scratch(in->device);
   in->stream = static_cast<hipStream_t>(hip_stream);
+  load_code_beside(in->stream);
   in->ws = static_cast<uint8_t*>(d_workspace);
   build_sites(l.L, J_host, &in->sites, &in->cm_of_site, &in->rowj);
   // PA_MODEL_GAUSS16: per (site, pattern) the LDS byte offset 8 max(dE16, 0)

@@ -325,6 +325,10 @@ constexpr uint32_t kProbeThreads = 2048 * 256;
 constexpr int kProbeValuOpsPerIter = 32;
 hipError_t launch_probe_valu(uint32_t* out, uint32_t iters, uint32_t form, hipStream_t stream);
 hipError_t launch_probe_philox(uint32_t* out, uint32_t calls, hipStream_t stream);
+// The code objects of every lattice size onto the current device (each is one object,
+// which HIP otherwise loads at its first launch, inside a caller's sweep, step, graph
+// capture or call that must not allocate: 1.2 to 2 ms; all of them 10 ms).
+hipError_t load_code();
 hipError_t launch_init(const DevPop& P, uint32_t cur, hipStream_t stream);
 // the slots r0 .. r1 - 1 (multiples of 32), [replica][site] int8 in device memory,
 // from buffer cur (R: replicas of the population) and back into it

@@ -2203,6 +2203,14 @@ void launch_link_overlap_l(const DevPop& a, const DevPop& b, uint32_t cur_a, uin
                      cur_b, part);
 }
 
+// Loads the code object of the kernels instantiated for L (asking for the attributes
+// of one of them does).
+template <int L>
+hipError_t load_code_l() {
+  hipFuncAttributes a;
+  return hipFuncGetAttributes(&a, reinterpret_cast<const void*>(k_sweep_pm<2, L, 8>));
+}
+
 // This file is compiled once per lattice size with PA_KERNEL_L = L, for the
 // kernels that are instantiated per L (one object each, built in parallel),
 // and once without it for everything else.
@@ -2217,8 +2225,11 @@ void launch_link_overlap_l(const DevPop& a, const DevPop& b, uint32_t cur_a, uin
 #ifdef PA_KERNEL_L
 PA_INSTANTIATE(, 1, PA_KERNEL_L)
 PA_INSTANTIATE(, 2, PA_KERNEL_L)
+template hipError_t load_code_l<PA_KERNEL_L>();
 #else
-#define PA_EXTERN_L(LL) PA_INSTANTIATE(extern, 1, LL) PA_INSTANTIATE(extern, 2, LL)
+#define PA_EXTERN_L(LL)                                       \
+  PA_INSTANTIATE(extern, 1, LL) PA_INSTANTIATE(extern, 2, LL) \
+  extern template hipError_t load_code_l<LL>();
 PA_EXTERN_L(4)
 PA_EXTERN_L(6)
 PA_EXTERN_L(8)
@@ -2227,6 +2238,15 @@ PA_EXTERN_L(12)
 PA_EXTERN_L(14)
 PA_EXTERN_L(16)
 #undef PA_EXTERN_L
+
+hipError_t load_code() {
+  for (const auto load : {load_code_l<4>, load_code_l<6>, load_code_l<8>, load_code_l<10>,
+                          load_code_l<12>, load_code_l<14>, load_code_l<16>}) {
+    const hipError_t e = load();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
 
 hipError_t launch_fill_u32(uint32_t* p, uint32_t value, size_t n, hipStream_t stream) {
   if (n == 0) return hipSuccess;
