@@ -79,3 +79,48 @@ def test_copy_step_spread(pam, layout, L, dbeta):
     o.sweep(dbeta, 1)
     assert_state(g, o)
     g.close()
+
+
+@pytest.mark.parametrize("layout", ["int8", "bitpack64"])
+@pytest.mark.parametrize("split", [4, 8])
+@pytest.mark.parametrize("L", [4, 6, 8, 10, 12, 14, 16])
+def test_infinite_temperature(pam, L, split, layout):
+    """beta = 0, where every move is taken: odd and even numbers of sweeps, with
+    and without a pending copy step, then sweeps with draws."""
+    R = 70
+    pam.pa_autotune_set(L, R, split, layout=layout)
+    g, o = pair(pam, L, R, 3 * L, layout)
+    for resample, beta, n in ((None, 0.0, 1), (None, 0.0, 2), (0.4, 0.0, 3), (None, 0.5, 1)):
+        for p in (g, o):
+            if resample is not None:
+                p.resample(resample)
+            p.sweep(beta, n)
+        assert_state(g, o)
+    pam.pa_autotune_reset()
+    g.close()
+
+
+def test_infinite_temperature_is_not_slower(pam):
+    """Ten sweeps at beta = 0 take no longer than ten with draws (through the pass
+    that serves any threshold they took three to five times as long)."""
+    import time
+
+    import torch
+
+    s = torch.cuda.Stream()
+    g = pam.Population(8, 20000, pa_inputs.couplings_pm(8, 1), 1, layout="bitpack64", stream=s)
+
+    def ms(beta):
+        best = 1e9
+        for _ in range(6):
+            s.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(10):
+                g.sweep(beta, 10)
+            s.synchronize()
+            best = min(best, 1e3 * (time.perf_counter() - t0))
+        return best
+
+    with_draws = ms(0.7)
+    assert ms(0.0) < 1.2 * with_draws
+    g.close()
