@@ -1668,6 +1668,52 @@ static uint32_t staged_replicas(const DevPop& P) {
   return P.layout == PA_LAYOUT_BITPACK64 ? P.capacity / 8 : P.capacity;
 }
 
+// Bytes of the tiles that hold R replicas.
+static size_t tiles_bytes(const DevPop& P, uint32_t R) {
+  return (size_t)((R + 63) / 64) * P.N * (P.layout == PA_LAYOUT_BITPACK64 ? 8 : 64);
+}
+
+// Spins of R replicas from the bytes of their tiles to the canonical layout on the
+// host, and (bit-packed) back into zeroed bytes.
+static void unpack_spins(const pa_instance* in, const uint8_t* tiles, uint32_t R, int8_t* out) {
+  const uint32_t N = in->dev.N;
+  for (uint32_t r = 0; r < R; ++r, out += N) {
+    const uint32_t lane = r & 63u;
+    if (in->dev.layout == PA_LAYOUT_BITPACK64) {
+      const uint8_t* const t = tiles + (size_t)(r >> 6) * N * 8 + (lane >> 3);
+      for (uint32_t s = 0; s < N; ++s)
+        out[s] = (int8_t)(1 - 2 * ((t[8 * in->cm_of_site[s]] >> (lane & 7u)) & 1));
+    } else {
+      const uint8_t* const t = tiles + (size_t)(r >> 6) * N * 64 + lane;
+      for (uint32_t s = 0; s < N; ++s) out[s] = (int8_t)t[64 * in->cm_of_site[s]] < 0 ? -1 : 1;
+    }
+  }
+}
+
+static void pack_spins(const pa_instance* in, const int8_t* spins, uint32_t R, uint8_t* tiles) {
+  const uint32_t N = in->dev.N;
+  for (uint32_t r = 0; r < R; ++r, spins += N) {
+    const uint32_t lane = r & 63u;
+    uint8_t* const t = tiles + (size_t)(r >> 6) * N * 8 + (lane >> 3);
+    for (uint32_t s = 0; s < N; ++s)
+      t[8 * in->cm_of_site[s]] |= (uint8_t)((spins[s] < 0 ? 1u : 0u) << (lane & 7u));
+  }
+}
+
+// Spins below which an export and an import convert on the host.  On the device each
+// piece (up to eight in the bit-packed layout) costs a launch and a copy of its own,
+// 20 to 30 us; the host takes about 0.4 ns a spin (us on the host / on the device, out:
+// bit-packed L = 4, 128000 spins 89 / 185, L = 6, 432000 spins 215 / 223, L = 8,
+// 512000 spins 252 / 218; int8 L = 6, 15120 spins 40 / 50, L = 4, 32000 spins 57 / 50; in:
+// bit-packed L = 6, 432000 spins 219 / 254, L = 4, 640000 spins 250 / 239; int8 never
+// more than 3 us faster on the host).
+static bool export_on_host(const DevPop& P, uint32_t R) {
+  return (uint64_t)R * P.N < (P.layout == PA_LAYOUT_BITPACK64 ? 430000u : 30000u);
+}
+static bool import_on_host(const DevPop& P, uint32_t R) {
+  return P.layout == PA_LAYOUT_BITPACK64 && (uint64_t)R * P.N < 640000u;
+}
+
 int pa_export_state(pa_instance* in, int8_t* spins_host, uint32_t* U_host, uint32_t* family_host,
                     uint32_t* R_tilde) {
   if (int rc0 = enter(in)) return rc0;
@@ -1685,7 +1731,11 @@ int pa_export_state(pa_instance* in, int8_t* spins_host, uint32_t* U_host, uint3
     PA_HIP(in, hipMemcpy(U_host, P.U[in->cur], (size_t)R * 4, hipMemcpyDeviceToHost));
   if (family_host && R)
     PA_HIP(in, hipMemcpy(family_host, P.fam[in->cur], (size_t)R * 4, hipMemcpyDeviceToHost));
-  if (spins_host && R) {
+  if (spins_host && R && export_on_host(P, R)) {
+    std::vector<uint8_t> tiles(tiles_bytes(P, R));
+    PA_HIP(in, hipMemcpy(tiles.data(), P.spins[in->cur], tiles.size(), hipMemcpyDeviceToHost));
+    unpack_spins(in, tiles.data(), R, spins_host);
+  } else if (spins_host && R) {
     // the population's other buffer is free between calls: converted there and
     // copied out, as many replicas at a time as it holds
     const uint32_t per = staged_replicas(P);
@@ -1736,19 +1786,25 @@ int pa_import_state(pa_instance* in, const int8_t* spins_host, const uint32_t* f
   int rc = materialize(in);  // drop nothing silently: finish a pending copy first
   if (rc) return rc;
   PA_HIP(in, hipStreamSynchronize(in->stream));
-  // staged in the population's other buffer and converted, as many replicas at a
-  // time as it holds; the last slots of the last tile are cleared
-  const uint32_t slots = (R_tilde + 63) / 64 * 64, per = staged_replicas(P);
-  int8_t* const stage = static_cast<int8_t*>(P.spins[in->cur ^ 1u]);
-  for (uint32_t r0 = 0; r0 < slots; r0 += per) {
-    const uint32_t r1 = std::min(r0 + per, slots);
-    if (r0 < R_tilde)
-      PA_HIP(in, hipMemcpyAsync(stage, spins_host + (size_t)r0 * P.N,
-                                (size_t)(std::min(r1, R_tilde) - r0) * P.N, hipMemcpyHostToDevice,
-                                in->stream));
-    PA_HIP(in, pa::launch_import_spins(P, in->cur, stage, R_tilde, r0, r1, in->stream));
+  if (R_tilde && import_on_host(P, R_tilde)) {
+    std::vector<uint8_t> tiles(tiles_bytes(P, R_tilde), 0);
+    pack_spins(in, spins_host, R_tilde, tiles.data());
+    PA_HIP(in, hipMemcpy(P.spins[in->cur], tiles.data(), tiles.size(), hipMemcpyHostToDevice));
+  } else {
+    // staged in the population's other buffer and converted, as many replicas at a
+    // time as it holds; the last slots of the last tile are cleared
+    const uint32_t slots = (R_tilde + 63) / 64 * 64, per = staged_replicas(P);
+    int8_t* const stage = static_cast<int8_t*>(P.spins[in->cur ^ 1u]);
+    for (uint32_t r0 = 0; r0 < slots; r0 += per) {
+      const uint32_t r1 = std::min(r0 + per, slots);
+      if (r0 < R_tilde)
+        PA_HIP(in, hipMemcpyAsync(stage, spins_host + (size_t)r0 * P.N,
+                                  (size_t)(std::min(r1, R_tilde) - r0) * P.N,
+                                  hipMemcpyHostToDevice, in->stream));
+      PA_HIP(in, pa::launch_import_spins(P, in->cur, stage, R_tilde, r0, r1, in->stream));
+    }
+    PA_HIP(in, hipStreamSynchronize(in->stream));
   }
-  PA_HIP(in, hipStreamSynchronize(in->stream));
   if (R_tilde)
     PA_HIP(in, hipMemcpy(P.fam[in->cur], family_host, (size_t)R_tilde * 4, hipMemcpyHostToDevice));
   DevScalars sc{};
