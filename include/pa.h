@@ -355,7 +355,7 @@ size_t pa_batch_workspace_bytes(uint32_t n_pops, uint32_t n_pairs, uint32_t n_st
  * overlap histogram (pa_overlap_hist's binning) is recorded after every step;
  * may be NULL when n_pairs = 0.  The caller owns d_workspace
  * (pa_batch_workspace_bytes bytes) until pa_batch_free.  A batch of several lattice
- * sizes runs part of its sweeps on a stream of its own, made here on the device of
+ * sizes may run part of its sweeps on a stream of its own, made here on the device of
  * the instances' stream (default priority, all compute units) and ordered within the
  * steps on that stream by events.  Synchronises. */
 int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* pairs,
@@ -396,7 +396,7 @@ size_t pa_stepper_workspace_bytes(uint32_t max_pops, uint32_t max_L);
 /* Create a stepper that launches on hip_stream (every instance it steps must
  * have been created on that stream).  A stepper of several instances also makes a
  * stream of its own on the same device (default priority, all compute units): a step
- * over several lattice sizes runs part of its sweeps there, ordered within the step
+ * over several lattice sizes may run part of its sweeps there, ordered within the step
  * on hip_stream by events.  The caller owns d_workspace
  * (pa_stepper_workspace_bytes bytes, 256-byte aligned) until pa_stepper_free.
  * libpa allocates a pinned host staging image of the same size. */

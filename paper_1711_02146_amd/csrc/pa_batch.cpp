@@ -127,7 +127,7 @@ int capture_step(pa_batch* b) {
   const auto sweep = [&](const pa_batch::SweepGroup& sg, hipStream_t st) {
     return pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, st);
   };
-  ok = ok && pa_host::launch_sweeps(b->g_sweep, b->side, s, sweep) == hipSuccess;
+  ok = ok && pa_host::launch_sweeps(b->g_sweep, b->side, true, s, sweep) == hipSuccess;
   ok = ok && pa::launch_hist_family(B, b->g_post, b->max_levels, s) == hipSuccess &&
        pa::launch_record(B, b->g_perpop, s) == hipSuccess;
   for (const auto& pg : b->g_pairs)
@@ -331,7 +331,8 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
       pa::launch_hist(B, b->g_hist, b->max_levels, false, s) != hipSuccess)
     return fail(PA_EDEVICE);
   if (hipStreamSynchronize(s) != hipSuccess) return fail(PA_EDEVICE);
-  if (b->g_sweep.size() > 1) b->side.create(s);
+  if (pa_host::batch_beside(pa_host::beside_us(b->g_sweep, n_sweeps), n_steps))
+    b->side.create(s);
   const int rc = capture_step(b);
   if (rc) return fail(rc);
   for (uint32_t p = 0; p < n_pops; ++p) pops[p]->in_batch = true;

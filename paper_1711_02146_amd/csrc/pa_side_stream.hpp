@@ -65,13 +65,35 @@ struct SideStream {
   }
 };
 
-// The launches of a set's sweep groups (launch(group, stream)) on `stream` and the
-// side stream, the largest first (the groups are put in that order), each on the one
-// with less work so far; what follows on `stream` waits for both.
+// What a second stream can hide of a set's sweep launches, in microseconds: all but the
+// longest, each about 5 and, per sweep, 2 and its attempts (work: sites x tiles) at
+// 1e12/s.
+template <typename SweepGroup>
+double beside_us(const std::vector<SweepGroup>& groups, uint32_t n_sweeps) {
+  double sum = 0.0, most = 0.0;
+  for (const SweepGroup& g : groups) {
+    const double us = 5.0 + n_sweeps * (2.0 + 64e-6 * (double)g.work);
+    sum += us;
+    most = std::max(most, us);
+  }
+  return sum - most;
+}
+// Below these the launches stay on one stream.  A stepper's step: fork and join take the
+// host about 15 us (us a step on one stream / on two, 1 sweep: L = 4 and 6, R = 500 85 /
+// 103, with three lattice sizes 128 / 126; 3 sweeps 99 / 105 and L = 4 and 8 109 / 103; 10
+// sweeps 146 / 134).  A batch's graph: about 7 of these us a step (1 sweep 44 / 49, 2
+// sweeps 51 / 51, 5 sweeps 71 / 62), and 100 to 250 once, to make the stream and a graph
+// of two branches.
+constexpr double kStepBesideUs = 12.0;
+inline bool batch_beside(double us, uint32_t n_steps) { return n_steps * (us - 7.0) > 200.0; }
+
+// The launches of a set's sweep groups (launch(group, stream)) on `stream` and, with
+// `beside`, the side stream, the largest first (the groups are put in that order), each
+// on the one with less work so far; what follows on `stream` waits for both.
 template <typename SweepGroup, typename Launch>
-hipError_t launch_sweeps(std::vector<SweepGroup>& groups, const SideStream& side,
+hipError_t launch_sweeps(std::vector<SweepGroup>& groups, const SideStream& side, bool beside,
                          hipStream_t stream, Launch launch) {
-  const bool two = side.s && groups.size() > 1;
+  const bool two = beside && side.s && groups.size() > 1;
   // (in place: nothing here allocates, so nothing can throw between fork and join)
   std::sort(groups.begin(), groups.end(),
             [](const SweepGroup& a, const SweepGroup& b) { return a.work > b.work; });

@@ -237,7 +237,9 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
   const auto sweep = [&](const SweepGroup& sg, hipStream_t where) {
     return pa::launch_sweep(B, sg.g, sg.layout, sg.L, sg.split, pa::kModelPm, where);
   };
-  ok = ok && pa_host::launch_sweeps(g_sweep, s->side, st, sweep) == hipSuccess;
+  const bool beside = pa_host::beside_us(g_sweep, *std::max_element(n_sweeps, n_sweeps + n)) >=
+                      pa_host::kStepBesideUs;
+  ok = ok && pa_host::launch_sweeps(g_sweep, s->side, beside, st, sweep) == hipSuccess;
   ok = ok && pa::launch_hist_family(B, g_post, max_levels, st) == hipSuccess &&
        pa::launch_record(B, g_perpop, st) == hipSuccess;
   if (!ok) return dev_fail();

@@ -1,9 +1,11 @@
 // The sweep launches of a set on two streams (pa_side_stream.hpp), compiled for the
 // CPU against the few HIP calls it makes, here on a machine of two devices with
 // HIP's rules: streams and events are made on the current device, and an event is
-// recorded only in a stream of its own device.  argv: the current device and the
-// device of the set's stream.  Prints the result of the launches, how many went to
-// the set's stream, to a second stream of the same device and to anything else, and
+// recorded only in a stream of its own device.  argv: the current device, the device of
+// the set's stream and, for the rules of when the second stream is used, the sweeps of a
+// step, the steps of a batch (0: a stepper) and the work (sites x tiles) of each launch.
+// Prints the result of the launches, how many went to the set's stream, to a second
+// stream of the same device and to anything else, whether they came largest first, and
 // the current device afterwards.
 #include <cstdint>
 #include <cstdio>
@@ -50,17 +52,25 @@ struct Group {
   uint64_t work;
 };
 
-int main(int, char** argv) {
+int main(int argc, char** argv) {
   const int dev = std::atoi(argv[2]);
   hipSetDevice(std::atoi(argv[1]));
   Stream set{dev};
   pa_host::SideStream side;
   side.create(&set);
   std::vector<Group> groups = {{3}, {10}, {5}};
+  bool second = true;
+  if (argc > 4) {
+    groups.clear();
+    for (int i = 5; i < argc; ++i) groups.push_back({std::strtoull(argv[i], nullptr, 10)});
+    const int n_steps = std::atoi(argv[4]);
+    const double us = pa_host::beside_us(groups, (uint32_t)std::atoi(argv[3]));
+    second = n_steps ? pa_host::batch_beside(us, (uint32_t)n_steps) : us >= pa_host::kStepBesideUs;
+  }
   int own = 0, beside = 0, elsewhere = 0;
   uint64_t last = ~0ull;
   bool ordered = true;
-  const hipError_t e = pa_host::launch_sweeps(groups, side, &set, [&](const Group& g, hipStream_t s) {
+  const hipError_t e = pa_host::launch_sweeps(groups, side, second, &set, [&](const Group& g, hipStream_t s) {
     ordered = ordered && g.work <= last;
     last = g.work;
     ++(s == &set ? own : s->dev == dev ? beside : elsewhere);
