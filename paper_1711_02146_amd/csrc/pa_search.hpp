@@ -11,9 +11,12 @@
 //     above some energy, and the sum of tau_i (<E>_w - E_i) over them is minus
 //     a covariance of E with an increasing function of E.
 //   - An evaluation is off by at most eta(x) = eta0 + eta1 x (cull_eta).  So if
-//     eps(a) + 2 eta(a) <= target, every mid <= a has eps(mid) <= target, and if
-//     eps(b) - 2 eta(b) > target, every mid >= b has eps(mid) > target: those
-//     halvings are decided without an evaluation.
+//     eps(a) + 2 eta(a) <= target, every mid <= a has eps(mid) <= target; if eps(x) -
+//     eta(x) - eta(c) > target, every mid from x to c has eps(mid) > target.  With c =
+//     rem this holds for every mid from some x = far up, with c = far for every mid
+//     from some b <= far to far, so for all from b up.  (far lies next to the crossing
+//     after a round or two, so eta(far) is hardly more than eta(b).)  Those halvings
+//     are decided without an evaluation.
 //   - A first few rounds of up to kCullLanes evaluations close [a, b] in on the
 //     crossing by interpolation; the halvings left between a and b (about the
 //     last twelve) are evaluated, three at a time where evaluations run side by
@@ -44,6 +47,7 @@ struct CullSearch {
   double eta0, eta1;               // error bound of an evaluation at x: eta0 + eta1 x
   double lo, hi;                   // the bisection's interval after `it` halvings
   double a, b;                     // decided: taken at and below a, not taken at and above b
+  double far;                      // not taken at and above, by the bound at rem (b <= far)
   double x[kCullLanes];            // candidates of the round
   double e[kCullLanes];            // their culling fractions
   double px[4], pe[4];             // evaluated points next to the crossing, ascending in x: two
@@ -80,6 +84,7 @@ PA_HD inline void cull_start(CullSearch& s, double rem, double target, double ep
   s.hi = rem;
   s.a = 0.0;       // eps(0) <= target: mid = 0 occurs only as lo itself
   s.b = 2.0 * rem;
+  s.far = 2.0 * rem;
   s.it = 0;
   s.round = 0;
   s.result = eps0 > target ? -1 : 0;
@@ -195,12 +200,20 @@ PA_HD inline void cull_advance(CullSearch& s) {
     s.result = 1;
     return;
   }
+  const double eta_rem = s.eta0 + s.eta1 * s.rem;
   PA_UNROLL
   for (int k = 0; k < kCullLanes; ++k) {
     if (k >= s.n) continue;
-    const double margin = 2.0 * (s.eta0 + s.eta1 * s.x[k]);
-    if (s.e[k] + margin <= s.target && s.x[k] > s.a) s.a = s.x[k];
-    if (s.e[k] - margin > s.target && s.x[k] < s.b) s.b = s.x[k];
+    const double eta = s.eta0 + s.eta1 * s.x[k];
+    if (s.e[k] + 2.0 * eta <= s.target && s.x[k] > s.a) s.a = s.x[k];
+    if (s.e[k] - (eta + eta_rem) > s.target && s.x[k] < s.far) s.far = s.x[k];
+  }
+  const double eta_far = s.eta0 + s.eta1 * (s.far < s.rem ? s.far : s.rem);
+  PA_UNROLL
+  for (int k = 0; k < kCullLanes; ++k) {
+    if (k >= s.n) continue;
+    const double eta = s.eta0 + s.eta1 * s.x[k];
+    if (s.e[k] - (eta + eta_far) > s.target && s.x[k] < s.b) s.b = s.x[k];
   }
   if (s.round < kCullInterp) cull_points(s);
   ++s.round;

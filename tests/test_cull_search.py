@@ -26,3 +26,15 @@ def test_search_equals_bisection(program, lanes, sums):
     assert n == 1500 and bad == 0 and p.returncode == 0
     assert rounds <= (40 if lanes == 7 else 70)  # 64 halvings and the interpolation's rounds
     assert evals < 66 * n                        # the bisection's own count
+
+
+@pytest.mark.parametrize("lanes", [7, 3])
+def test_search_is_exact_within_the_evaluations_error_bound(tmp_path, lanes):
+    """Evaluations as far off as their bound allows, on curves that are flat next to
+    the target, with a bound that grows by much over the range: a candidate above the
+    target decides the ones beyond it only by the bound that holds there."""
+    exe = str(tmp_path / "cull_bounds_ref")
+    subprocess.check_call(["g++", "-O2", "-std=c++17", "-ffp-contract=off", "-I" + CSRC,
+                           os.path.join(HERE, "cull_bounds_ref.cpp"), "-o", exe])
+    bad, n = (int(v) for v in subprocess.check_output([exe, "20000", str(lanes)]).split())
+    assert n == 20000 and bad == 0
