@@ -423,20 +423,24 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
 int pa_stepper_free(pa_stepper* s);
 
 /* ------------------------------------------------------------------------ */
-/* Autotuner.  The sweep kernel (Sec. II MCMC sweeps, Sec. II.A model) runs   */
-/* one 64-replica tile per workgroup with 4 or 8 waves sharing it; which is   */
-/* faster depends on L, the number of tiles in the launch and the device.     */
-/* Both give the same bits.  A built-in rule measured on MI355X is used until */
-/* the autotuner has timed a shape in this process.                          */
+/* Autotuner.  The sweep kernels (Sec. II MCMC sweeps, Sec. II.A model) have  */
+/* two forms, called 4 and 8 after the waves that share a 64-replica tile:    */
+/* 8 is the shorter walk per tile, 4 the one that fills the chip (in some     */
+/* sizes by several tiles per workgroup).  Which is faster depends on L, the  */
+/* number of tiles in the launch and the device.  Both give the same bits.  A */
+/* built-in rule measured on MI355X is used until the autotuner has timed a   */
+/* shape in this process.                                                     */
 /* ------------------------------------------------------------------------ */
 
 /* Time n_sweeps-sweep launches of both forms on the instance (repeats times
  * each, at inverse temperature beta >= 0: the regime the caller will run in;
  * at beta = 0 no draw is made) and remember the faster for launches of the same
  * coupling model, spin layout, L and size class (floor(log2(tiles))), in this
- * process, for single instances, batches and steppers alike.  The population, its counters and
+ * process, for single instances, batches and steppers alike.  Where the built-in rule
+ * changes inside the class, only for the sizes on the measured one's side.  The
+ * population, its counters and
  * its results are not changed (the trial sweeps write only the spare buffer).
- * split_out (nullable): the chosen waves per tile; ms_out (nullable, 2
+ * split_out (nullable): the chosen form, 4 or 8; ms_out (nullable, 2
  * floats): average launch time of the 4- and 8-wave forms.  Needs no pending
  * copy step (PA_ESTATE).  Synchronises. */
 int pa_autotune_sweep(pa_instance* in, double beta, uint32_t n_sweeps, uint32_t repeats,
@@ -494,7 +498,7 @@ int pa_autotune_set_layout(uint32_t model, uint32_t L, uint64_t tiles, uint32_t 
 /* Pin the sweep form for a shape instead of timing it: launches of the
  * coupling model (PA_MODEL_*), spin layout (PA_LAYOUT_INT8 or
  * PA_LAYOUT_BITPACK64), L and size class of `tiles` (floor(log2(tiles)),
- * tiles = ceil(R~ / 64)) use `split` waves per tile (4 or 8) in this process,
+ * tiles = ceil(R~ / 64)) use the form `split` (4 or 8) in this process,
  * until pa_autotune_reset or another choice for the same shape.  The results
  * do not depend on it.  PA_EINVAL on an unknown model or layout, L outside
  * [4, 16] or odd, tiles = 0, or another split. */

@@ -482,12 +482,14 @@ inline uint32_t sweep_form(uint32_t model, uint32_t L, uint32_t split, uint64_t 
   if (model != kModelPm) return L > 10 ? split : split == 4 ? kGaussLds : kGaussLdsOne;
   return split == 4 && L <= 8 && tiles >= enough ? kPmPacked : split;
 }
-// The form a launch uses: sweep_form of the autotuner's choice for (model,
-// layout, L, size class of `tiles`) when one was measured in this process, else
-// of the default (pa_tune.cpp).
+// The form a launch uses: sweep_form of the choice set for (model, layout, L, size
+// class of `tiles`) or measured there in this process (by sizes inside the class, see
+// pa_tune.cpp), else of the default.
 uint32_t sweep_split_for(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles);
+// a choice measured at `tiles`, and one set for its size class
 void sweep_split_record(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles,
                         uint32_t split);
+void sweep_split_set(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles, uint32_t split);
 
 // Spin layout of a population created with the library's choice, when the
 // autotuner has not timed its shape: bit-packed (one bit per spin, 64

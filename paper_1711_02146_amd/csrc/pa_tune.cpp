@@ -1,7 +1,13 @@
 // pa_tune.cpp -- device measurement: the autotuner's two tables and the probes
 // of the device's VALU and Philox ceilings.  The split table holds, per
-// coupling model, spin layout, L and size class of a sweep launch, the number
-// of waves per tile that measured fastest on this device; the layout table
+// coupling model, spin layout, L and size class of a sweep launch, the choice (4 or
+// 8, see sweep_form) that measured fastest on this device and the size it was measured
+// at, or the choice that a caller set for the class.  The rules that a measured choice
+// stands in for change inside a size class (several tiles per workgroup from some size
+// up; at L = 10 with Gaussian couplings by rounds of workgroups: 512 tiles 0.152 ms on
+// two tiles against 0.168 on one, 768 tiles 0.293 against 0.256), so a launch takes it
+// where the choice is between the same kernels and the rule answers as at the measured
+// size, and the rule's choice elsewhere.  The layout table
 // holds, per coupling model, L and size class, the spin layout whose sweep
 // measured fastest (the layout PA_LAYOUT_AUTO resolves to at creation).  Size
 // class = floor(log2(tiles)).  Neither choice changes a result (every draw is
@@ -18,7 +24,11 @@
 namespace {
 
 std::mutex g_mu;
-std::map<std::tuple<uint32_t, uint32_t, uint32_t, uint32_t>, uint32_t> g_table;
+struct SplitChoice {
+  uint32_t split;
+  uint64_t tiles;  // measured at; 0: set by a caller, for the whole class
+};
+std::map<std::tuple<uint32_t, uint32_t, uint32_t, uint32_t>, SplitChoice> g_table;
 std::map<std::tuple<uint32_t, uint32_t, uint32_t>, uint32_t> g_layouts;
 
 uint32_t size_class(uint64_t tiles) {
@@ -35,18 +45,29 @@ uint32_t size_class(uint64_t tiles) {
 namespace pa {
 
 uint32_t sweep_split_for(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles) {
+  const uint32_t rule = sweep_split_default(model, L, tiles);
   {
     std::lock_guard<std::mutex> lk(g_mu);
     const auto it = g_table.find({model, layout, L, size_class(tiles)});
-    if (it != g_table.end()) return sweep_form(model, L, it->second, tiles);
+    if (it != g_table.end()) {
+      const SplitChoice& c = it->second;
+      if (c.tiles == 0 || (sweep_form(model, L, 4, tiles) == sweep_form(model, L, 4, c.tiles) &&
+                           rule == sweep_split_default(model, L, c.tiles)))
+        return sweep_form(model, L, c.split, tiles);
+    }
   }
-  return sweep_form(model, L, sweep_split_default(model, L, tiles), tiles);
+  return sweep_form(model, L, rule, tiles);
 }
 
 void sweep_split_record(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles,
                         uint32_t split) {
   std::lock_guard<std::mutex> lk(g_mu);
-  g_table[{model, layout, L, size_class(tiles)}] = split;
+  g_table[{model, layout, L, size_class(tiles)}] = {split, tiles};
+}
+
+void sweep_split_set(uint32_t model, uint32_t layout, uint32_t L, uint64_t tiles, uint32_t split) {
+  std::lock_guard<std::mutex> lk(g_mu);
+  g_table[{model, layout, L, size_class(tiles)}] = {split, 0};
 }
 
 uint32_t layout_for(uint32_t model, uint32_t L, uint64_t tiles) {
@@ -87,7 +108,7 @@ extern "C" int pa_autotune_set(uint32_t model, uint32_t layout, uint32_t L, uint
   if (layout != PA_LAYOUT_INT8 && layout != PA_LAYOUT_BITPACK64) return PA_EINVAL;
   if (L < 4 || L > (uint32_t)pa::kMaxL || (L & 1u) || tiles == 0) return PA_EINVAL;
   if (split != 4 && split != 8) return PA_EINVAL;
-  pa::sweep_split_record(model, layout, L, tiles, split);
+  pa::sweep_split_set(model, layout, L, tiles, split);
   return PA_OK;
 }
 
