@@ -124,3 +124,25 @@ def test_infinite_temperature_is_not_slower(pam):
     with_draws = ms(0.7)
     assert ms(0.0) < 1.2 * with_draws
     g.close()
+
+
+# the packed kernels of L = 6 (a tile per wave) and 8 (two waves per tile) at their own
+# sizes, with a part-filled last workgroup and last tile; L = 4 packs at any size
+@pytest.mark.parametrize("layout", ["int8", "bitpack64"])
+@pytest.mark.parametrize("L,R,few", [(4, 64 * 9 + 5, 2.0), (6, 64 * 1501 + 33, 1.2),
+                                     (8, 64 * 3201 + 1, 0.8)])
+def test_packed_forms_every_branch(pam, layout, L, R, few):
+    """A threshold of 2^32 for every move (beta = 0, odd and even numbers of sweeps) and
+    for some (1e-17), the largest below 2^32 (3e-17), a copy step to a handful of
+    survivors (sources spread over many old tiles) and all thresholds 0 (beta = 20)."""
+    pam.pa_autotune_set(L, R, 4, layout=layout)
+    g, o = pair(pam, L, R, 41 + L, layout)
+    for resample, beta, n in ((None, 0.0, 1), (None, 0.0, 2), (None, 1e-17, 1), (None, 3e-17, 1),
+                              (few, few, 1), (None, 20.0, 1)):
+        for p in (g, o):
+            if resample is not None:
+                p.resample(resample)
+            p.sweep(beta, n)
+        assert_state(g, o)
+    pam.pa_autotune_reset()
+    g.close()
