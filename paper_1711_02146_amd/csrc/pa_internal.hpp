@@ -450,8 +450,9 @@ inline uint32_t sweep_blocks(uint32_t model, uint32_t L, uint32_t split, uint32_
 // 0.044; L = 8, 157 tiles 0.059 / 0.070, 313 tiles 0.087 / 0.087; L = 10, 313
 // tiles 0.140 / 0.152, 782 tiles 0.247 / 0.243) and from L = 12 up, where eight
 // waves still have a full chunk each (L = 12, 3125 tiles 1.152 / 1.175; L = 16,
-// 1563 tiles 1.52 / 1.92); at L = 6 four are never slower (157 tiles 0.046 /
-// 0.046, 1563 tiles 0.186 / 0.132).
+// 1563 tiles 1.52 / 1.92); at L = 6, whose walk per wave is short either way, where a
+// launch leaves most CUs a tile each (8 tiles 0.050 / 0.048, 64 tiles 0.044 / 0.047, 256
+// tiles 0.043 / 0.047, 320 tiles 0.063 / 0.054, 1563 tiles 0.186 / 0.132).
 // Gaussian models, L <= 10: several tiles per workgroup (4) once that fills the
 // chip, one (8) below (ms per launch of 10 sweeps with several / one, real
 // couplings: L = 4, 768 tiles 0.055 / 0.046, 1024 tiles 0.054 / 0.062; L = 6, 313
@@ -463,7 +464,8 @@ inline uint32_t sweep_blocks(uint32_t model, uint32_t L, uint32_t split, uint32_
 // rounds decide.  From L = 12 up (k_sweep: the table does not fit) eight waves.
 inline uint32_t sweep_split_default(uint32_t model, uint32_t L, uint64_t tiles) {
   if (model == kModelPm) {
-    const uint64_t few = L == 4 ? 512 : L == 6 ? 0 : L == 8 ? 256 : 768;
+    if (L == 6) return tiles >= 48 && tiles <= 256 ? 8u : 4u;
+    const uint64_t few = L == 4 ? 512 : L == 8 ? 256 : 768;
     return L >= 12 || tiles < few ? 8u : 4u;
   }
   if (L == 10) return 5 * ((tiles + 511) / 512) < 3 * ((tiles + 255) / 256) ? 4u : 8u;

@@ -62,3 +62,11 @@ def test_set_choice_holds_in_the_whole_class(tune):
     assert form(GAUSS, BIT, 10, 512) == SEVERAL and form(GAUSS, BIT, 10, 768) == SEVERAL
     pam.pa_autotune_set(6, 64 * 1100, 4)
     assert form(PM, BIT, 6, 1100) == 4 and form(PM, BIT, 6, 1600) == PACKED
+
+
+def test_built_in_rule_at_l6(tune):
+    """+-J, L = 6: eight waves on a tile where a launch leaves most compute units one
+    tile each, four below and above."""
+    form, _ = tune
+    assert [form(PM, BIT, 6, t) for t in (1, 47, 48, 256, 257, 1499, 1500)] == [4, 4, 8, 8, 4, 4,
+                                                                                PACKED]
