@@ -328,7 +328,7 @@ int pa_batch_create(pa_instance* const* pops, uint32_t n_pops, const uint32_t* p
       return fail(PA_EDEVICE);
   }
   if (pa::launch_zero_acc(B, b->g_perpop, s) != hipSuccess ||
-      pa::launch_hist(B, b->g_hist, b->max_levels, false, s) != hipSuccess)
+      pa::launch_hist(B, b->g_hist, b->max_levels, s) != hipSuccess)
     return fail(PA_EDEVICE);
   if (hipStreamSynchronize(s) != hipSuccess) return fail(PA_EDEVICE);
   if (pa_host::batch_beside(pa_host::beside_us(b->g_sweep, n_sweeps), n_steps))

@@ -107,7 +107,6 @@ bool make_layout(const pa_params* p, Layout* out) {
   l.off_offsets = take((size_t)l.capacity * 4);
   l.off_src = take((size_t)l.capacity * 4);
   l.off_bsum = take((size_t)l.n_blocks * 4);
-  l.off_boff = take((size_t)l.n_blocks * 4);
   l.off_bcull = take((size_t)l.n_blocks * 4);
   // the histogram and the device scalars side by side: one copy brings both
   // to the host after a step (PA_MODEL_PM, whose histogram covers every level)
@@ -431,8 +430,7 @@ int fetch_hist(pa_instance* in, bool with_family) {
     PA_HIP(in, pa::launch_real_stats(B, group_of(in, in->d_meta->rsum, in->meta.rsum[1]),
                                      in->stream));
     if (with_family)
-      PA_HIP(in, pa::launch_family(B, group_of(in, in->d_meta->slots, in->meta.slots[1]), false,
-                                   in->stream));
+      PA_HIP(in, pa::launch_family(B, group_of(in, in->d_meta->slots, in->meta.slots[1]), in->stream));
     PA_HIP(in, hipMemcpyAsync(in->h_sc, P.sc, sizeof(DevScalars) + sizeof(pa::RealScalars),
                               hipMemcpyDeviceToHost, in->stream));
     PA_HIP(in, hipStreamSynchronize(in->stream));
@@ -457,11 +455,10 @@ int fetch_hist(pa_instance* in, bool with_family) {
                                       in->stream));
   } else {
     PA_HIP(in, pa::launch_hist(B, group_of(in, in->d_meta->hist, in->meta.hist[1]), P.n_levels,
-                               false, in->stream));
+                               in->stream));
   }
   if (with_family)
-    PA_HIP(in, pa::launch_family(B, group_of(in, in->d_meta->slots, in->meta.slots[1]), false,
-                                 in->stream));
+    PA_HIP(in, pa::launch_family(B, group_of(in, in->d_meta->slots, in->meta.slots[1]), in->stream));
   if (P.model == pa::kModelGauss16) {
     PA_HIP(in, hipMemcpyAsync(in->h_hist, P.hist, (size_t)n * 4, hipMemcpyDeviceToHost,
                               in->stream));
@@ -982,12 +979,11 @@ int queue_step_pm(pa_instance* in, double beta, uint32_t n_sweeps, uint32_t slot
   PA_HIP(in, launch_sweep_of(in, ps));
   const pa::BatchDev B = one_set(in, plain_step(in->cur ^ 1u));
   PA_HIP(in, pa::launch_hist(B, group_of(in, in->d_meta->hist, in->meta.hist[1]), P.n_levels,
-                             false, in->stream));
+                             in->stream));
   PA_HIP(in, hipMemcpyAsync(in->h_hist, P.hist, in->lay.hist_bytes + sizeof(DevScalars),
                             hipMemcpyDeviceToHost, in->stream));
   PA_HIP(in, hipEventRecord(in->ev_step, in->stream));
-  PA_HIP(in, pa::launch_family(B, group_of(in, in->d_meta->slots, in->meta.slots[1]), false,
-                               in->stream));
+  PA_HIP(in, pa::launch_family(B, group_of(in, in->d_meta->slots, in->meta.slots[1]), in->stream));
   PA_HIP(in, hipMemcpyAsync(in->h_eta2 + slot, &P.sc->sum_eta2, 8, hipMemcpyDeviceToHost,
                             in->stream));
   PA_HIP(in, hipEventRecord(in->ev_fam[slot], in->stream));
@@ -1236,7 +1232,6 @@ int init_instance(const pa_params* p, const int8_t* J_host, const std::vector<lo
   P.offsets = reinterpret_cast<uint32_t*>(w + l.off_offsets);
   P.src = reinterpret_cast<uint32_t*>(w + l.off_src);
   P.block_sums = reinterpret_cast<uint32_t*>(w + l.off_bsum);
-  P.block_offsets = reinterpret_cast<uint32_t*>(w + l.off_boff);
   P.block_culled = reinterpret_cast<uint32_t*>(w + l.off_bcull);
   P.hist = reinterpret_cast<uint32_t*>(w + l.off_hist);
   P.table = reinterpret_cast<pa::TableEntry*>(w + l.off_table);

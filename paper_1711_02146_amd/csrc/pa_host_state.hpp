@@ -33,7 +33,7 @@ struct Layout {
   uint32_t L, N, R, cap_limit, capacity, layout, n_levels, n_blocks, model, rowk_stride;
   size_t spins_bytes;
   size_t hist_bytes;  // the histogram's share of its block (n_levels words, 64-byte multiple)
-  size_t off_spins[2], off_U[2], off_fam[2], off_counts, off_offsets, off_src, off_bsum, off_boff,
+  size_t off_spins[2], off_U[2], off_fam[2], off_counts, off_offsets, off_src, off_bsum,
       off_bcull, off_hist, off_table, off_sites, off_psites, off_cm, off_rowj, off_rowk, off_gthr, off_ovl,
       off_lovl, off_lpart, off_sc, off_rs, off_pops, off_meta, off_rhe, off_rthr, off_rthr32, off_rpart, off_rsearch, off_gaddr;
   size_t total;

@@ -80,11 +80,11 @@ struct SiteEntry {
 };
 static_assert(sizeof(SiteEntry) == 16, "SiteEntry must be 16 bytes");
 
-// LDS address of the tile image in the sweep kernel: right after its 8-entry
-// threshold table, which sits at address 0 (the kernel checks both).
+// LDS address of the tile image in k_sweep: right after its first eight words, which
+// sit at address 0 (the kernel checks both).
 constexpr uint32_t kTileLdsBase = 64;
 
-// The same site for phase 1 of the colour passes (lane = site), laid out so
+// The same site for phase 1 of k_sweep's colour passes (lane = site), laid out so
 // that nothing needs unpacking: the LDS addresses kTileLdsBase + 8 nb[k] of
 // the six neighbours' words, and the coupling bits.  32 bytes: two 16-byte
 // loads per lane.
@@ -221,7 +221,6 @@ struct DevPop {
   uint32_t* offsets;            // exclusive scan of counts
   uint32_t* src;                // new slot -> old slot of the pending copy step
   uint32_t* block_sums;         // per block of kBlockCounts slots
-  uint32_t* block_offsets;
   uint32_t* block_culled;
   uint32_t* hist;               // n_levels
   struct TableEntry* table;     // n_levels: the resampling table by energy level
@@ -337,7 +336,7 @@ hipError_t launch_export_spins(const DevPop& P, uint32_t cur, int8_t* out, uint3
 hipError_t launch_import_spins(const DevPop& P, uint32_t cur, const int8_t* in, uint32_t R,
                                uint32_t r0, uint32_t r1, hipStream_t stream);
 hipError_t launch_zero_acc(const BatchDev& B, const Group& per_pop, hipStream_t stream);
-hipError_t launch_hist(const BatchDev& B, const Group& g, uint32_t max_levels, bool post,
+hipError_t launch_hist(const BatchDev& B, const Group& g, uint32_t max_levels,
                        hipStream_t stream);
 hipError_t launch_table(const BatchDev& B, const Group& per_pop, hipStream_t stream);
 hipError_t launch_counts(const BatchDev& B, const Group& g, hipStream_t stream);
@@ -355,7 +354,7 @@ hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint
 // workgroups each)
 hipError_t launch_hist_family(const BatchDev& B, const Group& g, uint32_t max_levels,
                               hipStream_t stream);
-hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream);
+hipError_t launch_family(const BatchDev& B, const Group& g, hipStream_t stream);
 hipError_t launch_record(const BatchDev& B, const Group& per_pop, hipStream_t stream);
 // overlap histograms of a batch step's pairs (blocks_overlap workgroups each)
 hipError_t launch_overlap(const BatchDev& B, const Group& pairs, const uint32_t* pair_pops,

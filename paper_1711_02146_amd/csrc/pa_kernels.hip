@@ -1055,10 +1055,9 @@ __device__ __forceinline__ void slot_words(const uint32_t* U, uint32_t i0, uint3
 // Energy histogram h_j = #{i < R~ : U_i = j} (the sum of Eq. 2 regrouped by
 // integer level), privatised in LDS; workgroup lb of a population takes its
 // lb-th kHistSlots slots.
-__device__ __forceinline__ void hist_body(const DevPop& P, const PopStep& sp, uint32_t lb,
-                                          uint32_t post) {
+__device__ __forceinline__ void hist_body(const DevPop& P, uint32_t cur, uint32_t lb) {
   extern __shared__ uint32_t h[];
-  const uint32_t* U = pick(P.U, post ? sp.cur ^ 1u : sp.cur);
+  const uint32_t* U = pick(P.U, cur);
   // the population's flag and size and the thread's slot words read together
   // (every slot below the capacity is allocated), then the flag checked
   const uint32_t dead = P.sc->dead, R = P.sc->R_tilde;
@@ -1077,9 +1076,9 @@ __device__ __forceinline__ void hist_body(const DevPop& P, const PopStep& sp, ui
     if (h[i]) atomicAdd(&P.hist[i], h[i]);
 }
 
-__global__ __launch_bounds__(256) void k_hist(BatchDev B, Group G, uint32_t post) {
+__global__ __launch_bounds__(256) void k_hist(BatchDev B, Group G) {
   const Member m = member_of(G);
-  hist_body(B.pops[m.pop], step_of(B, m.pop), m.lb, post);
+  hist_body(B.pops[m.pop], step_of(B, m.pop).cur, m.lb);
 }
 
 // Position of this thread's element among the flagged elements of the block,
@@ -1107,13 +1106,12 @@ __device__ uint32_t block_compact_pos(bool flag, uint32_t* wcount, uint32_t* tot
 
 // kModelGauss16: lowest and highest E16 of the population.  Each workgroup
 // takes kHistSlots slots, reduces them, and adds one atomic min and max.
-__global__ __launch_bounds__(256) void k_minmax(BatchDev B, Group G, uint32_t post) {
+__global__ __launch_bounds__(256) void k_minmax(BatchDev B, Group G) {
   __shared__ int32_t smin[256 / kWave], smax[256 / kWave];
   const Member m = member_of(G);
   const DevPop P = B.pops[m.pop];
   if (P.sc->dead) return;
-  const PopStep sp = step_of(B, m.pop);
-  const uint32_t* U = pick(P.U, post ? sp.cur ^ 1u : sp.cur);
+  const uint32_t* U = pick(P.U, step_of(B, m.pop).cur);
   const uint32_t R = P.sc->R_tilde;
   const uint32_t i0 = m.lb * kHistSlots, i1 = min(R, i0 + kHistSlots);
   if (i0 >= R) return;
@@ -1507,8 +1505,10 @@ __global__ __launch_bounds__(64 * SPLIT)
 __attribute__((amdgpu_waves_per_eu(sweep_min_waves_per_eu<L, M>()))) void k_sweep(BatchDev B,
                                                                                 Group G) {
   constexpr uint32_t N = L * L * L;
-  __shared__ unsigned long long thr_of_nu[8];  // first LDS object: its address, 0, is the base of
-                                               // the absolute LDS addresses below
+  // First LDS object, one word written so that it stays: its address, 0, is the base of
+  // the absolute LDS addresses below.  (Addressed from the image instead, without it, the
+  // quantised sweeps take 1 to 2% longer: L = 12, R = 1e5 1.156 -> 1.170 ms.)
+  __shared__ unsigned long long thr_of_nu[8];
   extern __shared__ uint32_t lds_all[];
   const Member m = member_of(G);
   const DevPop P = B.pops[m.pop];
@@ -1675,11 +1675,11 @@ __global__ __launch_bounds__(64) void k_energy(BatchDev B, Group G) {
 // the first kFamilyBlocks workgroups of a population work (the rest leave at
 // once), each over a stride of the slots, so that few atomic adds reach the
 // population's counter.
-__device__ __forceinline__ void family_body(const DevPop& P, const PopStep& sp, uint32_t lb,
-                                            uint32_t blocks, uint32_t post) {
+__device__ __forceinline__ void family_body(const DevPop& P, uint32_t cur, uint32_t lb,
+                                            uint32_t blocks) {
   __shared__ unsigned long long scratch[256 / kWave];
   if (P.sc->dead) return;
-  const uint32_t* fam = pick(P.fam, post ? sp.cur ^ 1u : sp.cur);
+  const uint32_t* fam = pick(P.fam, cur);
   const uint64_t R = P.sc->R_tilde;
   unsigned long long sq = 0;
   for (uint64_t i = (uint64_t)lb * 256 + threadIdx.x; i < R; i += (uint64_t)blocks * 256) {
@@ -1705,10 +1705,10 @@ __device__ __forceinline__ void family_body(const DevPop& P, const PopStep& sp, 
   if (threadIdx.x == 0 && s) atomicAdd(&P.sc->sum_eta2, s);
 }
 
-__global__ __launch_bounds__(256) void k_family(BatchDev B, Group G, uint32_t post) {
+__global__ __launch_bounds__(256) void k_family(BatchDev B, Group G) {
   const Member m = member_of(G);
   if (m.lb >= kFamilyBlocks) return;
-  family_body(B.pops[m.pop], step_of(B, m.pop), m.lb, kFamilyBlocks, post);
+  family_body(B.pops[m.pop], step_of(B, m.pop).cur, m.lb, kFamilyBlocks);
 }
 
 // Histogram and family sum of a set after its sweeps in one launch: the first
@@ -1720,9 +1720,9 @@ __global__ __launch_bounds__(256) void k_hist_family(BatchDev B, Group G) {
   const DevPop& P = B.pops[m.pop];
   const uint32_t nh = (P.capacity + kHistSlots - 1) / kHistSlots;
   if (m.lb < nh)
-    hist_body(P, step_of(B, m.pop), m.lb, 1u);
+    hist_body(P, step_of(B, m.pop).cur ^ 1u, m.lb);
   else
-    family_body(P, step_of(B, m.pop), m.lb - nh, m.nb - nh, 1u);
+    family_body(P, step_of(B, m.pop).cur ^ 1u, m.lb - nh, m.nb - nh);
 }
 
 // Post-step record of a batch step: integer sum of E over the population, the
@@ -2130,6 +2130,8 @@ void launch_sweep_l(const BatchDev& B, const Group& g, uint32_t split, uint32_t 
     const dim3 grid(g.blocks), block(64 * pm_waves(split));
     if (split == 8)
       hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, 8>), grid, block, lds_pm, stream, B, g);
+    else if constexpr (L == 4)  // four waves always pack several tiles (sweep_form)
+      hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, kPmPacked>), grid, block, lds_pm, stream, B, g);
     else if (split == kPmPacked && L <= 8)
       hipLaunchKernelGGL((k_sweep_pm<LAYOUT, L, L <= 8 ? kPmPacked : 4>), grid, block, lds_pm,
                          stream, B, g);
@@ -2296,17 +2298,16 @@ hipError_t launch_zero_acc(const BatchDev& B, const Group& g, hipStream_t stream
   return hipGetLastError();
 }
 
-hipError_t launch_hist(const BatchDev& B, const Group& g, uint32_t max_levels, bool post,
+hipError_t launch_hist(const BatchDev& B, const Group& g, uint32_t max_levels,
                        hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
-  hipLaunchKernelGGL(k_hist, dim3(g.blocks), dim3(256), (size_t)max_levels * 4, stream, B, g,
-                     post ? 1u : 0u);
+  hipLaunchKernelGGL(k_hist, dim3(g.blocks), dim3(256), (size_t)max_levels * 4, stream, B, g);
   return hipGetLastError();
 }
 
 hipError_t launch_minmax(const BatchDev& B, const Group& g, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
-  hipLaunchKernelGGL(k_minmax, dim3(g.blocks), dim3(256), 0, stream, B, g, 0u);
+  hipLaunchKernelGGL(k_minmax, dim3(g.blocks), dim3(256), 0, stream, B, g);
   return hipGetLastError();
 }
 
@@ -2376,6 +2377,7 @@ hipError_t launch_sweep(const BatchDev& B, const Group& g, uint32_t layout, uint
         g.n == 1))
     return hipErrorInvalidValue;
   if (split >= 4 && model != kModelPm && L <= 10) return hipErrorInvalidValue;
+  if (split == 4 && model == kModelPm && L == 4) return hipErrorInvalidValue;
   if (layout == 2) {
     PA_L_SWITCH_S(launch_sweep_l, 2)
   } else {
@@ -2405,9 +2407,9 @@ hipError_t launch_hist_family(const BatchDev& B, const Group& g, uint32_t max_le
   return hipGetLastError();
 }
 
-hipError_t launch_family(const BatchDev& B, const Group& g, bool post, hipStream_t stream) {
+hipError_t launch_family(const BatchDev& B, const Group& g, hipStream_t stream) {
   if (!g.blocks) return hipSuccess;
-  hipLaunchKernelGGL(k_family, dim3(g.blocks), dim3(256), 0, stream, B, g, post ? 1u : 0u);
+  hipLaunchKernelGGL(k_family, dim3(g.blocks), dim3(256), 0, stream, B, g);
   return hipGetLastError();
 }
 

@@ -230,7 +230,7 @@ int pa_stepper_step(pa_stepper* s, pa_instance* const* pops, uint32_t n, const d
   const size_t bytes = l.off_E + e_used * 8;
   if (hipMemcpyAsync(w, img, bytes, hipMemcpyHostToDevice, st) != hipSuccess) return dev_fail();
   bool ok = pa::launch_zero_acc(B, g_perpop, st) == hipSuccess &&
-            pa::launch_hist(B, g_hist, max_levels, false, st) == hipSuccess &&
+            pa::launch_hist(B, g_hist, max_levels, st) == hipSuccess &&
             pa::launch_table(B, g_perpop, st) == hipSuccess &&
             pa::launch_counts(B, g_slots, st) == hipSuccess &&
             pa::launch_scan_scatter(B, g_slots, st) == hipSuccess;
