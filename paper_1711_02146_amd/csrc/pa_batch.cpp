@@ -7,8 +7,8 @@
 //
 // A step of the graph, for every population of the batch:
 //   table (device FP64; exp row of the step from the host)  -> counts -> scan
-//   -> scatter -> sweep (one launch per (layout, L) group, fused copy)
-//   -> zero accumulators -> histogram -> family sums -> record -> overlaps
+//   and copy map (which clear the accumulators) -> sweep (one launch per (layout,
+//   L) group, fused copy) -> histogram and family sums -> record -> overlaps
 //   -> advance the device step counter.
 // The per-step parameters of every population are laid out in device memory
 // at creation and indexed by the step counter, so the same graph is replayed
@@ -46,7 +46,8 @@ bool batch_layout(uint32_t n_pops, uint32_t n_pairs, uint32_t n_steps, uint32_t 
   BatchLayout l{};
   const uint64_t N = (uint64_t)max_L * max_L * max_L;
   l.e_stride = (size_t)(3 * N + 1);
-  // group tables: 3 groups of (n pop ids + n + 1 starts), sweep groups
+  // group tables: 4 groups of (n pop ids + n + 1 starts; per population, slots,
+  // histogram, histogram and families), sweep groups
   // (n ids + n + 16 starts), pair groups (n_pairs ids + n_pairs + 2 starts)
   // and the 2 n_pairs pair members
   l.n_u32 = 4 * (2 * (size_t)n_pops + 1) + (2 * (size_t)n_pops + 16) + 4 * (size_t)n_pairs + 2;

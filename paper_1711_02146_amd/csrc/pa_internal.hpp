@@ -34,10 +34,8 @@ constexpr int kBlockCounts = 256;  // slots per block in the copy-count / scatte
 constexpr int kHistSlots = 4096;   // slots per block of the histogram kernel
 constexpr int kWindowLdsLevels = 16384;  // largest E16 window counted in LDS (64 KiB)
 constexpr int kMaxL = 16;
-// Sweep: per wave, one byte for each of 64 sites x 64 replicas (phase 1 of
-// the colour pass: one site per lane): the threshold byte address (+-J) or
-// the neighbour pattern (Gaussian couplings).  With the 8 KB tile image at L = 10, eight such areas leave four
-// workgroups of eight waves (eight waves per SIMD) in a CU's 160 KB.
+// k_sweep (Gaussian couplings, L >= 12): per wave, one byte for each of 64 sites x 64
+// replicas, the neighbour pattern (phase 1 of the colour pass: one site per lane).
 constexpr uint32_t kPlaneAreaBytes = 64 * 64;
 constexpr uint32_t kOverlapTiles = 8;  // 64-pair tiles (one wave each) per workgroup of k_overlap
 constexpr uint32_t kLinkCopies = 32;  // partial link-overlap histograms (see launch_link_overlap)
@@ -110,8 +108,10 @@ __host__ __device__ constexpr uint32_t pm_tiles(uint32_t L, uint32_t split) {
 
 // The Gaussian sweep with its table in LDS (k_sweep_gauss, L <= 10): waves and tiles
 // per workgroup, bytes of a wave's plane area (16 sites x 64 replicas, one byte
-// each), waves per SIMD that its registers are budgeted for (as many as the LDS
-// lets run, at most five), and the workgroups that fill 256 CUs.
+// each), waves per SIMD that its registers are budgeted for (as many as the LDS lets
+// run at L = 10, one workgroup of 16 waves), and the workgroups that fill 256 CUs.  With
+// 128 registers L = 8 on several tiles keeps 39 to 53 more in scratch memory (152 to 208
+// bytes a lane); the other sizes and the one-tile forms keep none there.
 constexpr uint32_t kGaussLds = 2;     // several tiles per workgroup
 constexpr uint32_t kGaussLdsOne = 3;  // one tile, for launches that leave the chip idle
 constexpr uint32_t kGaussPlaneBytes = 16 * 64;
@@ -456,7 +456,8 @@ inline uint32_t sweep_blocks(uint32_t model, uint32_t L, uint32_t split, uint32_
 // chip, one (8) below (ms per launch of 10 sweeps with several / one, real
 // couplings: L = 4, 768 tiles 0.055 / 0.046, 1024 tiles 0.054 / 0.062; L = 6, 313
 // tiles 0.098 / 0.055, 1024 tiles 0.102 / 0.102, 1536 tiles 0.134 / 0.148; L = 8,
-// 1024 tiles 0.165 / 0.176, 1536 tiles 0.266 / 0.256, 2048 tiles 0.327 / 0.351).  At
+// 1024 tiles 0.165 / 0.176, 1536 tiles 0.266 / 0.256, 2048 tiles 0.327 / 0.351: several
+// tiles are ahead where their rounds, of 1024 tiles, are full; one line at 1600).  At
 // L = 10 a workgroup fills a CU either way, a round of 256 workgroups takes 5 parts
 // of time with two tiles each against 3 with one (512 tiles 0.152 / 0.168, 768
 // tiles 0.293 / 0.256, 1024 tiles 0.292 / 0.327, 7813 tiles 2.27 / 2.45), and the

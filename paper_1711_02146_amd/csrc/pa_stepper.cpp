@@ -12,8 +12,8 @@
 // into the stepper's workspace with one host-to-device copy, then launches,
 // for every instance of the set at once:
 //   zero accumulators -> histogram (current population) -> FP64 table
-//   -> counts -> scan -> scatter -> fused copy + sweeps (one launch per
-//   (layout, L)) -> zero accumulators -> histogram -> family sums -> record,
+//   -> counts -> scan and copy map (which clear the accumulators again) -> fused copy +
+//   sweeps (one launch per (layout, L)) -> histogram and family sums -> record,
 // and reads the records back.  The arithmetic and the random numbers are
 // those of pa_resample + pa_sweep + pa_observables on each instance alone.
 #include <hip/hip_runtime.h>
@@ -44,8 +44,9 @@ bool stepper_layout(uint32_t max_pops, uint32_t max_L, StepperLayout* out) {
     return false;
   StepperLayout l{};
   const size_t N = (size_t)max_L * max_L * max_L;
-  // groups: per-pop, slots and histogram (n ids + n + 1 starts each), sweep
-  // groups (n ids + one start per group + n; at most 14 (layout, L) kinds)
+  // groups: per population, slots, histogram, histogram and families (n ids + n + 1
+  // starts each), sweep groups (n ids + one start per group + n; at most 14 (layout,
+  // L) kinds)
   l.n_u32 = 4 * (2 * (size_t)max_pops + 1) + (2 * (size_t)max_pops + 16);
   l.e_doubles = (size_t)max_pops * (3 * N + 1);
   size_t o = 0;
