@@ -98,16 +98,16 @@ BYTES_PER_REPLICA_FIXED = 20
 # lane-instructions per attempt = SQ_INSTS_VALU x 64 / attempts per launch.
 # None: no counters for the current source yet.
 PROFILE = {
-    "kernel_src_sha256": "cafc116031d74c0047471f25c6fce24502fc551232b38f298521264a061824e5",
+    "kernel_src_sha256": "4383d27170079ebe1d2075b4eea94da8a21e97e5d9914f46df4c872ff056ec05",
     # FETCH_SIZE KiB x 2 + WRITE_SIZE KiB x 1, per launch (profiles/*_hbm_counters.md)
-    "bytes_per_launch": (32873.3 * 2 + 64946.1) * 1024,
-    "gauss16_bytes_per_launch": (33243.9 * 2 + 64942.5) * 1024,
-    "real_bytes_per_launch": (37814.7 * 2 + 66898.5) * 1024,
-    "link_overlap_bytes_per_launch": (63921.8 * 2 + 10484.4) * 1024,
-    "int8_C2_bytes_per_launch": (25947.7 * 2 + 50797.2) * 1024,
-    "int8_overlap_bytes_per_call": (50037.0 * 2 + 51.9) * 1024,
-    # SQ_INSTS_VALU 1.0344e9 per launch x 64 lanes / 5.0e9 attempts
-    "valu_per_attempt": 1.0344e9 * 64 / 5.0e9,
+    "bytes_per_launch": (32865.4 * 2 + 64946.1) * 1024,
+    "gauss16_bytes_per_launch": (33243.8 * 2 + 64942.5) * 1024,
+    "real_bytes_per_launch": (37811.6 * 2 + 66898.5) * 1024,
+    "link_overlap_bytes_per_launch": (63913.3 * 2 + 10484.4) * 1024,
+    "int8_C2_bytes_per_launch": (25951.4 * 2 + 50797.2) * 1024,
+    "int8_overlap_bytes_per_call": (50037.6 * 2 + 51.9) * 1024,
+    # SQ_INSTS_VALU 1.0347e9 per launch x 64 lanes / 5.0e9 attempts
+    "valu_per_attempt": 1.0347e9 * 64 / 5.0e9,
 }
 
 
