@@ -94,4 +94,4 @@ def test_small_export_is_not_in_pieces():
         g.close()
         return best
 
-    assert us(2000) < 0.55 * us(10000)
+    assert us(2000) < 0.65 * us(10000)
